@@ -92,9 +92,17 @@ struct fftc_problem {
   Geo g;
   std::string err;
   DevState last{};
-  DevState init_host{};
+  struct HostSlot* slot = nullptr;   // host words of a running solve (see take_slot)
   std::vector<double> react_strong, react_weak;
   int profiling = 0;
+};
+
+// Host memory the device writes: the progress word of a running solve, which the host polls
+// instead of copying the state back, and the state and sums of a finished one.
+struct HostSlot {
+  unsigned progress;
+  unsigned pad[15];
+  fftc::SolveOut out;
 };
 
 struct fftc_batch {
@@ -124,6 +132,51 @@ int fail(fftc_problem* h, int code, const std::string& msg) {
     hipError_t e_ = (call);                                                         \
     if (e_ != hipSuccess) return fail(h, FFTC_E_HIP, std::string("HIP: ") + hipGetErrorString(e_)); \
   } while (0)
+
+// Slots of pinned host memory, one per handle that has solved, returned when it is destroyed: up to
+// 64 slabs of 64 (a handle beyond them, or one whose slab cannot be had, solves without).  A slab
+// is freed with its last slot, except the first.
+constexpr size_t kSlotBytes = (sizeof(HostSlot) + 127) / 128 * 128;
+struct SlotSlab {
+  char* base;
+  uint64_t used;
+};
+std::mutex g_slot_mu;
+SlotSlab g_slabs[64] = {};
+
+HostSlot* take_slot() {
+  std::lock_guard<std::mutex> lk(g_slot_mu);
+  for (SlotSlab& b : g_slabs) {
+    if (b.used == ~0ull) continue;
+    if (!b.base) {
+      void* p = nullptr;
+      if (hipHostMalloc(&p, 64 * kSlotBytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+      }
+      b.base = (char*)p;
+    }
+    const int k = __builtin_ctzll(~b.used);
+    b.used |= 1ull << k;
+    return (HostSlot*)(b.base + k * kSlotBytes);
+  }
+  return nullptr;
+}
+
+void give_slot(HostSlot* s) {
+  if (!s) return;
+  std::lock_guard<std::mutex> lk(g_slot_mu);
+  for (SlotSlab& b : g_slabs) {
+    const ptrdiff_t d = b.base ? (char*)s - b.base : -1;
+    if (d < 0 || d >= (ptrdiff_t)(64 * kSlotBytes)) continue;
+    b.used &= ~(1ull << (d / (ptrdiff_t)kSlotBytes));
+    if (!b.used && &b != g_slabs) {
+      (void)hipHostFree(b.base);
+      b.base = nullptr;
+    }
+    return;
+  }
+}
 
 bool factor_ok(int n, std::vector<int>& rad) {
   rad.clear();
@@ -456,20 +509,50 @@ int inc_period(const fftc_problem* h) {
   return h->cfg.anchor_every;
 }
 
-void enqueue_delta_iteration(fftc_problem* h, StageTimer* tm) {
+// Kernels that iteration `it` of a solve may select (L_*); fine: the passes are known to form
+// FP64 stresses from here on.  Every launch left out was one that would have returned at once
+// (1.5 to 2 us each on grids whose whole iteration takes 60 to 100 us).
+int launches_of(const fftc_problem* h, int it, bool fine) {
+  int w = L_ALL;
+  if (h->delta_mode) {
+    const int k = inc_period(h);
+    if (fine) {
+      w &= ~(L_U | L_INC);
+    } else if (k > 0) {
+      if (it % k == 0) w &= ~L_INC;
+      // between anchors a pass from u in FP32 follows only an incremental pass below tol; with
+      // the refinement threshold at or above tol that pass has switched to FP64 stresses
+      else if (h->cfg.tol == 0.0 || h->cfg.refine_below >= h->cfg.tol) w &= ~L_U;
+    }
+  }
+  // without contact the Anderson index is the iteration
+  if (!h->has_sphere && h->cfg.acv == FFTC_ACV_P) {
+    if (it < 1) w &= ~L_STORE;
+    if (it < 4 || it % h->cfg.period != 0) w &= ~L_ACCEL;
+  }
+  return w;
+}
+
+enum { HEAD = 1, TAIL = 2 };   // up to the equilibrium test, and the rest of an iteration
+
+void enqueue_delta_iteration(fftc_problem* h, StageTimer* tm, int which, int parts) {
   DeltaBufs<float> D = dbufs(h);
   const ContactDev ct = contact_dev(h);
   const WeakDev w = weak_dev(h);
   const StrongDev sd = strong_dev(h);
   const long long n3 = 3 * h->Nn;
   hipStream_t s = h->stream;
-  if (tm) tm->mark(s);
-  const int nres = launch_delta_residual<float>(h->g, D, ct, h->st, h->part, h->nblk_res, h->cfg.refine_below > 0.0,
-                                                inc_period(h) > 0, s);
-  if (tm) tm->mark(s);
-  launch_delta_control<float>(h->g, D, ct, w, h->st, h->part, h->wpart, nres, s);
-  if (tm) tm->mark(s);
-  if (h->cfg.acv == FFTC_ACV_P) launch_delta_anderson<float>(D, n3, h->st, h->gpart, h->nblk_res, s);
+  if (parts & HEAD) {
+    if (tm) tm->mark(s);
+    const int nres = launch_delta_residual<float>(h->g, D, ct, h->st, h->part, h->nblk_res, h->cfg.refine_below > 0.0,
+                                                  inc_period(h) > 0, which, s);
+    if (tm) tm->mark(s);
+    launch_delta_control<float>(h->g, D, ct, w, h->st, h->part, h->wpart, nres, s);
+    if (tm) tm->mark(s);
+  }
+  if (!(parts & TAIL)) return;
+  if (h->cfg.acv == FFTC_ACV_P && (which & L_ACCEL))
+    launch_delta_anderson<float>(D, n3, h->st, h->gpart, h->nblk_res, s);
   if (tm) tm->mark(s);
   for (int p = 0; p < TP_N; ++p) {
     launch_dtt<float>(delta_pass(h, p, D), h->ept, s);
@@ -480,9 +563,9 @@ void enqueue_delta_iteration(fftc_problem* h, StageTimer* tm) {
 }
 
 template <typename T>
-void enqueue_iteration(fftc_problem* h, StageTimer* tm = nullptr) {
+void enqueue_iteration(fftc_problem* h, StageTimer* tm = nullptr, int which = L_ALL, int parts = HEAD | TAIL) {
   if (h->delta_mode) {
-    enqueue_delta_iteration(h, tm);
+    enqueue_delta_iteration(h, tm, which, parts);
     return;
   }
   Bufs<T> B = bufs<T>(h);
@@ -491,20 +574,23 @@ void enqueue_iteration(fftc_problem* h, StageTimer* tm = nullptr) {
   const StrongDev sd = strong_dev(h);
   const long long n3 = 3 * h->Nn;
   hipStream_t s = h->stream;
-  if (h->cfg.acv == FFTC_ACV_U) {
-    Bufs<T> Bu = B;
-    Bu.X = B.u;  // residual store on the displacement
-    launch_flags_combine<T>(B, n3, h->st, 0, s);
-    launch_anderson<T>(Bu, n3, h->st, h->gpart, h->nblk_res, s);
-    launch_flags_combine<T>(B, n3, h->st, 1, s);
+  if (parts & HEAD) {
+    if (h->cfg.acv == FFTC_ACV_U) {
+      Bufs<T> Bu = B;
+      Bu.X = B.u;  // residual store on the displacement
+      launch_flags_combine<T>(B, n3, h->st, 0, s);
+      launch_anderson<T>(Bu, n3, h->st, h->gpart, h->nblk_res, L_ALL, s);
+      launch_flags_combine<T>(B, n3, h->st, 1, s);
+    }
+    if (tm) tm->mark(s);
+    launch_residual<T>(h->g, B, ct, h->st, h->part, h->nblk_res, 0, 0, s);
+    if (tm) tm->mark(s);
+    launch_weak<T>(h->g, B, w, h->st, 0, s);
+    launch_control(h->st, h->part, h->nblk_res, h->wpart, w.m, ct, kPartStride, s);
+    if (tm) tm->mark(s);
   }
-  if (tm) tm->mark(s);
-  launch_residual<T>(h->g, B, ct, h->st, h->part, h->nblk_res, 0, 0, s);
-  if (tm) tm->mark(s);
-  launch_weak<T>(h->g, B, w, h->st, 0, s);
-  launch_control(h->st, h->part, h->nblk_res, h->wpart, w.m, ct, kPartStride, s);
-  if (tm) tm->mark(s);
-  if (h->cfg.acv == FFTC_ACV_P) launch_anderson<T>(B, n3, h->st, h->gpart, h->nblk_res, s);
+  if (!(parts & TAIL)) return;
+  if (h->cfg.acv == FFTC_ACV_P) launch_anderson<T>(B, n3, h->st, h->gpart, h->nblk_res, which, s);
   if (tm) tm->mark(s);
   enqueue_green<T>(h, h->cfg.acv == FFTC_ACV_P ? SRC_ANDERSON : SRC_BUF, B.X, h->cfg.acv == FFTC_ACV_P, 0, tm);
   launch_proj<T>(h->g, B.u, w, ct, sd, h->st, 1, 0, s);
@@ -580,7 +666,7 @@ int profile_t(fftc_problem* h, int iters, double* ms, int nst) {
 
 // ---- solve = init + device-driven iterations + finish (shared by solo and batched solves)
 
-int init_state(fftc_problem* h) {
+int init_state(fftc_problem* h, unsigned* progress) {
   DevState hs{};
   hs.tol = h->cfg.tol;
   hs.gate = h->cfg.update_gate;
@@ -593,54 +679,60 @@ int init_state(fftc_problem* h) {
   hs.inc_k = inc_period(h);
   hs.best_res = 1e300;
   hs.best_it = 0;
-  h->init_host = hs;
-  HIPCHK(h, hipMemcpyAsync(h->st, &h->init_host, sizeof(DevState), hipMemcpyHostToDevice, h->stream));
+  hs.progress = progress;
+  launch_set_state(h->st, hs, h->stream);
+  HIPCHK(h, hipGetLastError());
   return FFTC_OK;
 }
 
 template <typename T>
-int init_literal(fftc_problem* h, const double* u_dev, int zero_start) {
+int init_literal(fftc_problem* h, const double* u_dev, int zero_start, unsigned* progress) {
   Bufs<T> B = bufs<T>(h);
   hipStream_t s = h->stream;
   const long long n3 = 3 * h->Nn;
   if (zero_start || !u_dev) HIPCHK(h, hipMemsetAsync(B.u, 0, sizeof(T) * n3, s));
-  else launch_convert<double, T>(u_dev, B.u, n3, s, 1.0 / h->hlen);
-  launch_zero_amask<T>(h->g, B.u, s);
+  else {
+    launch_convert<double, T>(u_dev, B.u, n3, s, 1.0 / h->hlen);
+    launch_zero_amask<T>(h->g, B.u, s);
+  }
   const ContactDev ct = contact_dev(h);
   // initial proj_U (and the initial active set from the gaps)
   if (ct.on) launch_contact_init<T>(h->g, B.u, ct, s);
   launch_proj<T>(h->g, B.u, weak_dev(h), ct, strong_dev(h), h->st, 0, 1, s);
-  return init_state(h);
+  return init_state(h, progress);
 }
 
-int init_delta(fftc_problem* h, const double* u_dev, int zero_start) {
+// Of the residual form's fields only u needs a start: every other one is written before its
+// first use (delta, t and p by the first iteration; R, dY and c from the iterations on that the
+// Gram pass and the residual pass read them from).
+int init_delta(fftc_problem* h, const double* u_dev, int zero_start, unsigned* progress) {
   DeltaBufs<float> D = dbufs(h);
   hipStream_t s = h->stream;
   const long long n3 = 3 * h->Nn;
   if (zero_start || !u_dev) HIPCHK(h, hipMemsetAsync(D.u, 0, 8 * n3, s));
   else if (h->hlen != 1.0) launch_convert<double, double>(u_dev, D.u, n3, s, 1.0 / h->hlen);
   else HIPCHK(h, hipMemcpyAsync(D.u, u_dev, 8 * n3, hipMemcpyDeviceToDevice, s));
-  launch_zero_amask<double>(h->g, D.u, s);
+  if (!zero_start && u_dev) launch_zero_amask<double>(h->g, D.u, s);
   const ContactDev ct = contact_dev(h);
   if (ct.on) launch_contact_init<double>(h->g, D.u, ct, s);
   launch_delta_proj<float>(h->g, D, strong_dev(h), weak_dev(h), ct, h->st, 1, 0, s);
-  for (int q = 0; q < 11; ++q) HIPCHK(h, hipMemsetAsync(h->dfld[q], 0, 4 * n3, s));
-  return init_state(h);
+  return init_state(h, progress);
 }
 
-int solve_init(fftc_problem* h, const double* u_dev, int zero_start) {
+// progress: host word for the control step to write (fftc_solve polls it), or null
+int solve_init(fftc_problem* h, const double* u_dev, int zero_start, unsigned* progress = nullptr) {
   if (h->precision == FFTC_FP32 && h->cfg.acv == FFTC_ACV_U && h->nlit < 10)
     return fail(h, FFTC_E_STATE, "ACV_U in FP32 needs its Anderson fields: set it before binding the workspace");
   // FP32: residual-form iteration (FP64 displacement), except for ACV_U
   h->delta_mode = (h->precision == FFTC_FP32 && h->cfg.acv != FFTC_ACV_U) ? 1 : 0;
-  if (h->delta_mode) return init_delta(h, u_dev, zero_start);
-  return h->precision == FFTC_FP64 ? init_literal<double>(h, u_dev, zero_start)
-                                   : init_literal<float>(h, u_dev, zero_start);
+  if (h->delta_mode) return init_delta(h, u_dev, zero_start, progress);
+  return h->precision == FFTC_FP64 ? init_literal<double>(h, u_dev, zero_start, progress)
+                                   : init_literal<float>(h, u_dev, zero_start, progress);
 }
 
-void enqueue_iter(fftc_problem* h) {
-  if (h->precision == FFTC_FP64) enqueue_iteration<double>(h);
-  else enqueue_iteration<float>(h);
+void enqueue_iter(fftc_problem* h, int which = L_ALL, int parts = HEAD | TAIL) {
+  if (h->precision == FFTC_FP64) enqueue_iteration<double>(h, nullptr, which, parts);
+  else enqueue_iteration<float>(h, nullptr, which, parts);
 }
 
 int finish_report(fftc_problem* h, const DevState& out, double force_c, int nC, fftc_report* rep) {
@@ -669,33 +761,41 @@ int finish_report(fftc_problem* h, const DevState& out, double force_c, int nC, 
   return FFTC_OK;
 }
 
+constexpr int kForceRows = 64;   // blocks of the contact force (pairs in chk, the report after them)
+static_assert(8 * 2 * kForceRows + sizeof(SolveOut) <= sizeof(double) * 3 * 1024, "report in the check buffer");
+
 // After the iterations: reactions of the returned iterate, output displacement, report.
 int solve_finish(fftc_problem* h, double* u_dev, fftc_report* rep) {
   hipStream_t s = h->stream;
   const long long n3 = 3 * h->Nn;
   const ContactDev ct = contact_dev(h);
   const StrongDev sd = strong_dev(h);
-  HIPCHK(h, hipMemcpyAsync(&h->last, h->st, sizeof(DevState), hipMemcpyDeviceToHost, s));
-  std::vector<double> msp;
+  int ms_rows = 0;
   if (h->delta_mode) {
     DeltaBufs<float> D = dbufs(h);
     // the residual-form pass carries only the norms; the mean stress is formed here, once
-    msp.assign(6 * (size_t)launch_mean_stress_d<float>(h->g, D, h->part, s), 0.0);
-    HIPCHK(h, hipMemcpyAsync(msp.data(), h->part, 8 * msp.size(), hipMemcpyDeviceToHost, s));
+    ms_rows = launch_mean_stress_d<float>(h->g, D, h->part, s);
+    if (ct.on) launch_contact_force<double>(h->g, D.u, ct, h->chk, kForceRows, s);
+  } else if (ct.on) {
+    if (h->precision == FFTC_FP64) launch_contact_force<double>(h->g, bufs<double>(h).u, ct, h->chk, kForceRows, s);
+    else launch_contact_force<float>(h->g, bufs<float>(h).u, ct, h->chk, kForceRows, s);
+  }
+  // the state and these sums, straight to host memory where the handle has some
+  SolveOut* const dev_out = (SolveOut*)(h->chk + 2 * kForceRows);
+  launch_report(h->st, h->part, ms_rows, h->chk, ct.on ? kForceRows : 0, h->slot ? &h->slot->out : dev_out, s);
+  if (h->delta_mode) {
+    DeltaBufs<float> D = dbufs(h);
     launch_reactions_d<float>(h->g, D, sd, h->sreact, s);
     if (u_dev && h->hlen != 1.0) launch_convert<double, double>(D.u, u_dev, n3, s, h->hlen);
     else if (u_dev) HIPCHK(h, hipMemcpyAsync(u_dev, D.u, 8 * n3, hipMemcpyDeviceToDevice, s));
-    if (ct.on) launch_contact_force<double>(h->g, D.u, ct, h->chk, 64, s);
   } else if (h->precision == FFTC_FP64) {
     Bufs<double> B = bufs<double>(h);
     launch_reactions<double>(h->g, B, sd, h->sreact, s);
     if (u_dev) launch_convert<double, double>(B.u, u_dev, n3, s, h->hlen);
-    if (ct.on) launch_contact_force<double>(h->g, B.u, ct, h->chk, 64, s);
   } else {
     Bufs<float> B = bufs<float>(h);
     launch_reactions<float>(h->g, B, sd, h->sreact, s);
     if (u_dev) launch_convert<float, double>(B.u, u_dev, n3, s, h->hlen);
-    if (ct.on) launch_contact_force<float>(h->g, B.u, ct, h->chk, 64, s);
   }
   h->react_strong.assign(h->s_comp.size(), 0.0);
   h->react_weak.assign(h->w_comp.size(), 0.0);
@@ -703,47 +803,74 @@ int solve_finish(fftc_problem* h, double* u_dev, fftc_report* rep) {
     HIPCHK(h, hipMemcpyAsync(h->react_strong.data(), h->sreact, 8 * h->react_strong.size(), hipMemcpyDeviceToHost, s));
   if (!h->react_weak.empty())
     HIPCHK(h, hipMemcpyAsync(h->react_weak.data(), h->wreact, 8 * h->react_weak.size(), hipMemcpyDeviceToHost, s));
-  std::vector<double> cf(2 * 64, 0.0);
-  if (ct.on) HIPCHK(h, hipMemcpyAsync(cf.data(), h->chk, 8 * cf.size(), hipMemcpyDeviceToHost, s));
+  SolveOut host_out{};
+  if (!h->slot) HIPCHK(h, hipMemcpyAsync(&host_out, dev_out, sizeof(SolveOut), hipMemcpyDeviceToHost, s));
   HIPCHK(h, hipStreamSynchronize(s));
-  if (!msp.empty()) {
-    const size_t nb = msp.size() / 6;
-    for (int q = 0; q < 6; ++q) {
-      double a = 0.0;
-      for (size_t b = 0; b < nb; ++b) a += msp[6 * b + q];
-      h->last.ms[q] = a;
-    }
-  }
+  const SolveOut& out = h->slot ? h->slot->out : host_out;
+  h->last = out.state;
   const double h2 = h->hlen * h->hlen;   // forces: voxel units -> physical
   for (double& v : h->react_strong) v *= h2;
   for (double& v : h->react_weak) v *= h2;
   double force_c = 0.0;
   int nC = 0;
   if (ct.on) {
-    double fs = 0.0, cnt = 0.0;
-    for (int b = 0; b < 64; ++b) {
-      fs += cf[2 * b];
-      cnt += cf[2 * b + 1];
-    }
-    force_c = -((h->face % 2) ? 1.0 : -1.0) * fs * h2;
-    nC = (int)cnt;
+    force_c = -((h->face % 2) ? 1.0 : -1.0) * out.force * h2;
+    nC = (int)out.count;
   }
   return finish_report(h, h->last, force_c, nC, rep);
 }
 
+// Iterations in the queue ahead of the last equilibrium test the host has seen: enough that
+// the device never waits for the host (an iteration takes about 25 us to enqueue and 60 us or more
+// to run), and no more than two idle ones after the solve is over.
+constexpr int kAhead = 3;
+
 int solve_all(fftc_problem* h, double* u_dev, int zero_start, fftc_report* rep) {
-  int rc = solve_init(h, u_dev, zero_start);
+  if (!h->slot && h->static_dev < 0) h->slot = take_slot();   // (a static binding allocates nothing)
+  unsigned* const word = h->slot ? &h->slot->progress : nullptr;
+  if (word) __atomic_store_n(word, 0u, __ATOMIC_RELEASE);
+  int rc = solve_init(h, u_dev, zero_start, word);
   if (rc != FFTC_OK) return rc;
   hipStream_t s = h->stream;
-  int chunk = 4;
-  DevState out{};
-  for (;;) {
-    for (int t = 0; t < chunk; ++t) enqueue_iter(h);
-    HIPCHK(h, hipGetLastError());
-    HIPCHK(h, hipMemcpyAsync(&out, h->st, sizeof(DevState), hipMemcpyDeviceToHost, s));
-    HIPCHK(h, hipStreamSynchronize(s));
-    if (out.done) break;
-    chunk = std::min(64, chunk * 2);
+  // The control step ends the solve at iteration max_iter at the latest, in its first half.
+  const long long last = h->cfg.max_iter;
+  long long sent = 0;
+  bool fine = false;
+  auto send = [&]() {
+    enqueue_iter(h, launches_of(h, (int)sent, fine), sent < last ? HEAD | TAIL : HEAD);
+    ++sent;
+  };
+  if (!word) {
+    // no host word: poll the device state after chunks of growing length
+    int chunk = 4;
+    DevState out{};
+    do {
+      for (int t = 0; t < chunk && sent <= last; ++t) send();
+      HIPCHK(h, hipGetLastError());
+      HIPCHK(h, hipMemcpyAsync(&out, h->st, sizeof(DevState), hipMemcpyDeviceToHost, s));
+      HIPCHK(h, hipStreamSynchronize(s));
+      fine = out.fine != 0;
+      chunk = std::min(64, chunk * 2);
+    } while (!out.done && sent <= last);
+    return solve_finish(h, u_dev, rep);
+  }
+  for (unsigned spins = 0;;) {
+    const unsigned v = __atomic_load_n(word, __ATOMIC_ACQUIRE);
+    if (v & kProgressDone) break;
+    fine = (v & kProgressFine) != 0;
+    if (sent <= last && sent < (long long)(v & kProgressCount) + kAhead) {
+      send();
+      HIPCHK(h, hipGetLastError());
+      continue;
+    }
+    // wait for the next test; an idle or failed stream will write none
+    if (++spins % 4096 == 0 && hipStreamQuery(s) != hipErrorNotReady) {
+      HIPCHK(h, hipStreamSynchronize(s));
+      const unsigned w = __atomic_load_n(word, __ATOMIC_ACQUIRE);
+      if (!(w & kProgressDone) && (long long)(w & kProgressCount) < sent)
+        return fail(h, FFTC_E_HIP, "the iteration stopped without reporting");
+    }
+    __builtin_ia32_pause();
   }
   return solve_finish(h, u_dev, rep);
 }
@@ -829,7 +956,7 @@ int stage_residual_form_t(fftc_problem* h, const double* const* in, int il, int 
   const ContactDev ct = contact_dev(h);
   const WeakDev w = weak_dev(h);
   if (ct.on) launch_contact_init<double>(h->g, D.u, ct, s);
-  const int nres = launch_delta_residual<float>(h->g, D, ct, h->st, h->part, h->nblk_res, 1, kind == 2, s);
+  const int nres = launch_delta_residual<float>(h->g, D, ct, h->st, h->part, h->nblk_res, 1, kind == 2, L_ALL, s);
   launch_delta_control<float>(h->g, D, ct, w, h->st, h->part, h->wpart, nres, s);
   // R difference as the Gram pass forms it, from the R ring (staged in the transform buffer)
   if (out[2]) launch_diff<float>(Rcur, Rprev, D.t, n3, s);
@@ -926,6 +1053,7 @@ int fftc_create(fftc_h* out, const int32_t n[3], double hlen, int32_t scheme, in
 void fftc_destroy(fftc_h h) {
   if (!h) return;
   release_static(h);
+  give_slot(h->slot);
   delete h;
 }
 

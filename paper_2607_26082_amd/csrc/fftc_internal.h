@@ -71,7 +71,16 @@ struct DevState {
   double sing[6];     // singular-mode coefficients of u (comp, {theta = 0, theta = pi})
   double gamma[3];    // difference-form Anderson coefficients
   double best_res;    // FP32 form: residual at the last halving (stagnation test of the refinement)
+  unsigned* progress; // host word the control step writes (see kProgress*), or null
 };
+
+// Word the control step leaves for the host after every equilibrium test: the number of tests
+// done, whether the passes form FP64 stresses from now on (sticky), whether the solve is over.
+constexpr unsigned kProgressDone = 1u << 31, kProgressFine = 1u << 30, kProgressCount = kProgressFine - 1;
+
+// Kernels of one iteration that the device state may select; the host leaves out the ones it
+// knows cannot be.
+enum { L_U = 1, L_INC = 2, L_U64 = 4, L_STORE = 8, L_ACCEL = 16, L_ALL = 31 };
 
 enum StatusCode { ST_RUNNING = 0, ST_CONVERGED = 1, ST_NOCONV = 2, ST_NAN = 3 };
 

@@ -410,6 +410,7 @@ __global__ __launch_bounds__(kBlock) void k_control(DevState* st, const double* 
   const double tol = st->tol, gate = st->gate, refine_below = st->refine_below;
   const double best_res = st->best_res;
   const int best_it = st->best_it;
+  unsigned* const progress = st->progress;
   // the FP32 form's incremental pass forms no stress norm: the last full pass's is kept, and
   // such a pass never ends the solve (the exit test is taken on a pass from u)
   const bool inc = res_pass(st) == PASS_INC;
@@ -504,6 +505,10 @@ __global__ __launch_bounds__(kBlock) void k_control(DevState* st, const double* 
       if (inc && res < tol) st->inc_k = 0;
     }
     if (s_done) st->done = 1;
+    if (progress)
+      __hip_atomic_store(progress,
+                         (unsigned)(it + 1) | (st->fine ? kProgressFine : 0u) | (s_done ? kProgressDone : 0u),
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
   __syncthreads();
   if (s_done) return;
@@ -1035,11 +1040,43 @@ __global__ __launch_bounds__(kBlock) void k_contact_force(Geo g, const T* u, Con
 }
 
 // Re-arm the iteration state for `iters` more iterations (fixed-count runs).
+__global__ void k_set_state(DevState* st, DevState hs) { *st = hs; }
+
+__global__ __launch_bounds__(kBlock) void k_report(DevState* st, const double* __restrict__ ms, int ms_rows,
+                                                   const double* __restrict__ cf, int cf_rows,
+                                                   SolveOut* __restrict__ out) {
+  __shared__ double sh[6 * 16];
+  double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int r = threadIdx.x; r < ms_rows; r += blockDim.x)
+#pragma unroll
+    for (int q = 0; q < 6; ++q) acc[q] += ms[6 * r + q];
+  block_sum<6>(acc, sh);
+  if (threadIdx.x == 0) {
+    if (ms_rows > 0)
+#pragma unroll
+      for (int q = 0; q < 6; ++q) st->ms[q] = acc[q];
+    double f = 0.0, n = 0.0;
+    for (int r = 0; r < cf_rows; ++r) {
+      f += cf[2 * r];
+      n += cf[2 * r + 1];
+    }
+    out->force = f;
+    out->count = n;
+    __threadfence_block();
+  }
+  __syncthreads();
+  static_assert(sizeof(DevState) % 4 == 0, "copied by words");
+  const unsigned* src = (const unsigned*)st;
+  unsigned* dst = (unsigned*)&out->state;
+  for (unsigned w = threadIdx.x; w < sizeof(DevState) / 4; w += blockDim.x) dst[w] = src[w];
+}
+
 __global__ void k_extend(DevState* st, int iters, double tol) {
   st->done = 0;
   st->status = ST_RUNNING;
   st->max_iter = st->it + iters;
   st->tol = tol;
+  st->progress = nullptr;   // no solve is waiting for it
 }
 
 // ---------------------------------------------------------------------------
@@ -1069,9 +1106,10 @@ void launch_control(DevState* st, const double* part, int nblk, const double* wp
 }
 
 template <typename T>
-void launch_anderson(const Bufs<T>& B, long long n3, DevState* st, double* gpart, int nblk, hipStream_t s) {
-  hipLaunchKernelGGL(k_anderson_r<T>, dim3(nblk), dim3(kBlock), 0, s, B, n3, st, gpart);
-  hipLaunchKernelGGL(k_alpha, dim3(1), dim3(kBlock), 0, s, st, gpart, nblk);
+void launch_anderson(const Bufs<T>& B, long long n3, DevState* st, double* gpart, int nblk, int which, hipStream_t s) {
+  if (which & (L_STORE | L_ACCEL))
+    hipLaunchKernelGGL(k_anderson_r<T>, dim3(nblk), dim3(kBlock), 0, s, B, n3, st, gpart);
+  if (which & L_ACCEL) hipLaunchKernelGGL(k_alpha, dim3(1), dim3(kBlock), 0, s, st, gpart, nblk);
 }
 
 template <typename T>
@@ -1119,6 +1157,15 @@ void launch_zero_amask(const Geo& g, T* u, hipStream_t s) {
   hipLaunchKernelGGL(k_zero_amask<T>, dim3(grid_for(g.Nn, 8192)), dim3(kBlock), 0, s, g, u);
 }
 
+void launch_set_state(DevState* st, const DevState& hs, hipStream_t s) {
+  hipLaunchKernelGGL(k_set_state, dim3(1), dim3(1), 0, s, st, hs);
+}
+
+void launch_report(DevState* st, const double* ms, int ms_rows, const double* cf, int cf_rows, SolveOut* out,
+                   hipStream_t s) {
+  hipLaunchKernelGGL(k_report, dim3(1), dim3(kBlock), 0, s, st, ms, ms_rows, cf, cf_rows, out);
+}
+
 void launch_extend(DevState* st, int iters, double tol, hipStream_t s) {
   hipLaunchKernelGGL(k_extend, dim3(1), dim3(1), 0, s, st, iters, tol);
 }
@@ -1147,7 +1194,7 @@ void launch_scale(double* x, long long n, double f, hipStream_t s) {
   template void launch_residual<T>(const Geo&, const Bufs<T>&, const ContactDev&, DevState*, double*, int, int,   \
                                    int, hipStream_t);                                                                  \
   template void launch_weak<T>(const Geo&, const Bufs<T>&, const WeakDev&, DevState*, int, hipStream_t);         \
-  template void launch_anderson<T>(const Bufs<T>&, long long, DevState*, double*, int, hipStream_t);             \
+  template void launch_anderson<T>(const Bufs<T>&, long long, DevState*, double*, int, int, hipStream_t);        \
   template void launch_proj<T>(const Geo&, T*, const WeakDev&, const ContactDev&, const StrongDev&, DevState*,   \
                                int, int, hipStream_t);                                                            \
   template void launch_contact_init<T>(const Geo&, const T*, const ContactDev&, hipStream_t);                     \

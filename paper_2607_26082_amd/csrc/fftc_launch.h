@@ -13,11 +13,12 @@ void launch_control(DevState* st, const double* part, int nblk, const double* wp
                     const ContactDev& ct, int pstride, hipStream_t s);
 // Residual-form iteration, first half: the residual pass (returns the number of block
 // partial rows it wrote), then the average relations and the control step over those rows.
-// refine: also launch the FP64-stress pass (taken once the state's refinement flag is set);
-// inc: also launch the incremental pass (taken between the state's full passes).
+// refine: the solve may take the FP64-stress pass (once the state's refinement flag is set);
+// inc: it may take the incremental pass (between the state's full passes); which: the passes
+// (L_U, L_INC, L_U64) that this iteration may select.
 template <typename T>
 int launch_delta_residual(const Geo& g, const DeltaBufs<T>& D, const ContactDev& ct, DevState* st, double* part,
-                          int nblk, int refine, int inc, hipStream_t s);
+                          int nblk, int refine, int inc, int which, hipStream_t s);
 template <typename T>
 void launch_delta_control(const Geo& g, const DeltaBufs<T>& D, const ContactDev& ct, const WeakDev& w, DevState* st,
                           const double* part, const double* wpart, int nblk, hipStream_t s);
@@ -38,10 +39,20 @@ void launch_diff(const T* a, const T* b, T* out, long long n, hipStream_t s);
 // yz, xz, xy) times the voxel volume, rows of 6 in part; returns the number of rows.
 template <typename T>
 int launch_mean_stress_d(const Geo& g, const DeltaBufs<T>& D, double* part, hipStream_t s);
+// Device state set from a host copy (a kernel argument: no host-memory copy to wait for).
+void launch_set_state(DevState* st, const DevState& hs, hipStream_t s);
+// End of a solve: the mean-stress rows (ms_rows > 0) summed into the state, the state and the
+// contact-force rows (cf_rows) written to host memory the device can reach.
+struct SolveOut {
+  DevState state;
+  double force, count;   // contact: normal force and active nodes
+};
+void launch_report(DevState* st, const double* ms, int ms_rows, const double* cf, int cf_rows, SolveOut* out,
+                   hipStream_t s);
 template <typename T>
 void launch_reactions_d(const Geo& g, const DeltaBufs<T>& D, const StrongDev& sd, double* out, hipStream_t s);
 template <typename T>
-void launch_anderson(const Bufs<T>& B, long long n3, DevState* st, double* gpart, int nblk, hipStream_t s);
+void launch_anderson(const Bufs<T>& B, long long n3, DevState* st, double* gpart, int nblk, int which, hipStream_t s);
 template <typename T>
 void launch_flags_combine(const Bufs<T>& B, long long n3, DevState* st, int which, hipStream_t s);
 template <typename T>

@@ -950,7 +950,7 @@ int launch_delta_residual_ts(const Geo& g, const DeltaBufs<T>& D, const ContactD
 // small-strain problems without contact or singular modes (the caller's eligibility test).
 template <typename T>
 int launch_delta_residual(const Geo& g, const DeltaBufs<T>& D, const ContactDev& ct, DevState* st, double* part,
-                          int nblk, int refine, int inc, hipStream_t s) {
+                          int nblk, int refine, int inc, int which, hipStream_t s) {
   const bool gen = ct.on || g.sing[0] || g.sing[1] || g.sing[2];
   const bool use_inc = inc && !g.fs && !gen;
   // each pass on the grid for its own resident count (the incremental one's taken only when
@@ -963,12 +963,12 @@ int launch_delta_residual(const Geo& g, const DeltaBufs<T>& D, const ContactDev&
     const int rows = std::max(tf.rows, std::max(ti.rows, tu.rows));
     tf.rows = ti.rows = tu.rows = rows;
   }
-  const int rows = launch_delta_residual_ts<T, T>(g, D, ct, st, part, nblk, tf, s);
-  if (refine) launch_delta_residual_ts<T, double>(g, D, ct, st, part, nblk, tu, s);
-  if (use_inc && ti.tx > 0)
+  if (which & L_U) launch_delta_residual_ts<T, T>(g, D, ct, st, part, nblk, tf, s);
+  if (refine && (which & L_U64)) launch_delta_residual_ts<T, double>(g, D, ct, st, part, nblk, tu, s);
+  if (use_inc && ti.tx > 0 && (which & L_INC))
     hipLaunchKernelGGL((k_residual_dt<T, false, false, T, true>), dim3(ti.tx * ti.ty * ti.nseg), dim3(256), 0, s, g, D,
                        ct, st, part, ti);
-  return tf.tx > 0 ? tf.rows : rows;
+  return tf.tx > 0 ? tf.rows : nblk;
 }
 
 template <typename T>
@@ -1112,7 +1112,7 @@ void launch_weak_d_stage(const Geo& g, const DeltaBufs<T>& D, const WeakDev& w, 
 }
 
 template int launch_delta_residual<float>(const Geo&, const DeltaBufs<float>&, const ContactDev&, DevState*, double*,
-                                          int, int, int, hipStream_t);
+                                          int, int, int, int, hipStream_t);
 template void launch_delta_control<float>(const Geo&, const DeltaBufs<float>&, const ContactDev&, const WeakDev&,
                                           DevState*, const double*, const double*, int, hipStream_t);
 template void launch_delta_anderson<float>(const DeltaBufs<float>&, long long, DevState*, double*, int, hipStream_t);
