@@ -12,7 +12,7 @@ import sys
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-UNITS = ("fftc_dtt64.hip", "fftc_dtt32.hip", "fftc_residual.hip", "fftc_kernels.hip", "fftc_api.hip",
+UNITS = ("fftc_dtt64.hip", "fftc_dtt32.hip", "fftc_dense.hip", "fftc_residual.hip", "fftc_kernels.hip", "fftc_api.hip",
          "fftc_nn.hip")
 OUT = os.path.join(HERE, "libfftc.so")
 OBJDIR = os.path.join(HERE, "_build")

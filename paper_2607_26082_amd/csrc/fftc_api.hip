@@ -66,6 +66,9 @@ struct fftc_problem {
   // residual-form (FP32) fields: delta, e, p0, p1, R0, R1, dR0..2, dY0..2, t; FP64 u
   void* dfld[12] = {};
   double* u64 = nullptr;
+  // transform matrices of the axes that run as matrix products: per axis and transform type
+  // forward, inverse (null: the axis runs as FFTs)
+  double* mat[3][5] = {};
   int delta_mode = 0;
   void* lam = nullptr;
   void* mu = nullptr;
@@ -265,8 +268,20 @@ struct Layout {
   }
 };
 
-// carve the workspace; with base == nullptr only computes the size
-size_t carve(fftc_problem* h, char* base) {
+// Axes whose transforms run as matrix products (fftc_dense.hip): up to 256 nodes, every length
+// without a compile-time FFT and every periodic axis (per iteration, products against the
+// runtime-length FFT: 30x22x26 FP64 88 against 165 us, 75x140x18 FP32 139 against 256, 140^3 FP32
+// 692 against 1672 and FP64 832 against 1244, 256x256x16 periodic FP32 372 against 412); of the
+// compile-time lengths 16, 32 and 48 on grids of at most 160,000 nodes, where the passes are bound by
+// their chain of barriers (32^3 94 against 107 us in FP64; at 64^3 167 against 162).
+bool dense_axis(const fftc_problem* h, int J) {
+  if (h->N[J] > 256) return false;
+  return h->periodic[J] || !dtt_compiled(h->n[J]) || (h->precision == FFTC_FP32 && h->n[J] <= 48 && h->Nn <= 160000);
+}
+
+// carve the workspace; with base == nullptr only computes the size.  mats: with the transform
+// matrices (without them every axis runs as FFTs)
+size_t carve(fftc_problem* h, char* base, bool mats = true) {
   Layout L;
   const size_t ts = h->precision == FFTC_FP64 ? 8 : 4;
   const size_t f3 = ts * 3 * (size_t)h->Nn;
@@ -315,7 +330,17 @@ size_t carve(fftc_problem* h, char* base) {
   const int nd = h->precision == FFTC_FP32 ? 12 : 0;
   for (int i = 0; i < nd; ++i) off[q++] = L.take(4 * 3 * (size_t)h->Nn);
   if (nd) off[q++] = L.take(8 * 3 * (size_t)h->Nn);
+  // matrices: one forward and inverse pair per axis and type in use
+  size_t moff[3][5];
+  for (int J = 0; J < 3; ++J)
+    for (int t = 0; t < 5; ++t) {
+      moff[J][t] = (size_t)-1;
+      if (mats && dense_axis(h, J) && (h->type[0][J] == t || h->type[1][J] == t || h->type[2][J] == t))
+        moff[J][t] = L.take(2 * sizeof(double) * dense_mat_doubles(h->N[J]));
+    }
   if (base) {
+    for (int J = 0; J < 3; ++J)
+      for (int t = 0; t < 5; ++t) h->mat[J][t] = moff[J][t] == (size_t)-1 ? nullptr : (double*)(base + moff[J][t]);
     q = 0;
     h->nlit = nlit;
     for (int i = 0; i < 10; ++i) h->fld[i] = i < nlit ? base + off[q++] : nullptr;
@@ -458,6 +483,11 @@ DttArgs<T> dtt_args(fftc_problem* h, int axis, int mode, int force) {
   // form); any positive value is at least ~ a theta_min^2, far above this threshold
   for (int c = 0; c < 3; ++c) a.thr[c] = 1e-13 * std::max(h->g.ac[c][0], std::max(h->g.ac[c][1], h->g.ac[c][2]));
   a.nt = h->dtt_nt[pass_of(axis, mode)];
+  for (int c = 0; c < 3; ++c) {
+    const double* m = h->mat[axis][h->type[c][axis]];
+    a.mat[c][0] = m;
+    a.mat[c][1] = m ? m + dense_mat_doubles(h->N[axis]) : nullptr;
+  }
   return a;
 }
 
@@ -1354,7 +1384,7 @@ int fftc_workspace_bytes(fftc_h h, size_t* bytes) {
 namespace {
 // Binds ws to h: carves the fields, uploads tables and constraints, and (tune) times the two
 // block sizes of every transform pass; without tuning every pass takes the larger block.
-int bind_impl(fftc_h h, void* ws, size_t bytes, void* stream, bool tune) {
+int bind_impl(fftc_h h, void* ws, size_t bytes, void* stream, bool tune, bool mats = true) {
   if (!h || !ws) return FFTC_E_ARG;
   if (h->scheme == FFTC_HEX1 && h->precision != FFTC_FP64)
     return fail(h, FFTC_E_UNSUPPORTED, "the HEX1 scheme runs in FP64 (its hourglass modes have no FP32 residual form)");
@@ -1364,7 +1394,7 @@ int bind_impl(fftc_h h, void* ws, size_t bytes, void* stream, bool tune) {
     return fail(h, FFTC_E_UNSUPPORTED,
                 "the isotropic reference medium needs HEX1 and periodic axes or normal-mixed faces");
   if (((uintptr_t)ws) % kAlign) return fail(h, FFTC_E_WORKSPACE, "workspace must be 256-byte aligned");
-  const size_t need = carve(h, nullptr);
+  const size_t need = carve(h, nullptr, mats);
   if (bytes < need) return fail(h, FFTC_E_WORKSPACE, "workspace too small");
   // contact face nodes may not carry other constraints
   if (h->has_sphere) {
@@ -1384,8 +1414,12 @@ int bind_impl(fftc_h h, void* ws, size_t bytes, void* stream, bool tune) {
   h->ws = (char*)ws;
   h->ws_bytes = bytes;
   h->stream = (hipStream_t)stream;
-  carve(h, h->ws);
+  carve(h, h->ws, mats);
   hipStream_t s = h->stream;
+  for (int J = 0; J < 3; ++J)
+    for (int t = 0; t < 5; ++t)
+      if (h->mat[J][t])
+        launch_dense_mats(t, h->n[J], h->N[J], h->mat[J][t], h->mat[J][t] + dense_mat_doubles(h->N[J]), s);
   // geometry
   Geo& g = h->g;
   for (int J = 0; J < 3; ++J) {
@@ -1510,6 +1544,8 @@ int bind_impl(fftc_h h, void* ws, size_t bytes, void* stream, bool tune) {
     HIPCHK(h, hipEventCreate(&e1));
     const int cand[2] = {h->precision == FFTC_FP64 ? 128 : 256, h->precision == FFTC_FP64 ? 256 : 512};
     for (int p = 0; p < TP_N; ++p) {
+      h->dtt_nt[p] = cand[1];
+      if (h->periodic[axis[p]] || !dtt_compiled(h->n[axis[p]])) continue;   // one block size
       for (int v = 0; v < 2; ++v) {
         h->dtt_nt[p] = cand[v];
         float tot = 0.f;
@@ -1557,7 +1593,9 @@ int fftc_bind_workspace(fftc_h h, void* ws, size_t bytes, void* stream) {
 
 int fftc_bind_workspace_static(fftc_h h, void* stream) {
   if (!h) return FFTC_E_ARG;
-  const size_t need = carve(h, nullptr);
+  // (without the transform matrices where they would not fit)
+  const bool mats = carve(h, nullptr) <= kStaticWsBytes;
+  const size_t need = carve(h, nullptr, mats);
   if (need > kStaticWsBytes)
     return fail(h, FFTC_E_WORKSPACE, "problem needs " + std::to_string(need) + " bytes of workspace, the static "
                                      "workspace holds " + std::to_string(kStaticWsBytes));
@@ -1583,7 +1621,7 @@ int fftc_bind_workspace_static(fftc_h h, void* stream) {
     g_static_owner[dev] = h;
   }
   h->static_dev = dev;
-  const int rc = bind_impl(h, ptr, kStaticWsBytes, stream, false);
+  const int rc = bind_impl(h, ptr, kStaticWsBytes, stream, false, mats);
   if (rc != FFTC_OK) release_static(h);
   return rc;
 }

@@ -781,6 +781,10 @@ static void launch_dtt2_typed(const DttArgs<T>& a, hipStream_t s) {
 
 template <typename T>
 void launch_dtt(const DttArgs<T>& a, int ept, hipStream_t s) {
+  if (a.mat[0][0]) {
+    launch_dense<T>(a, s);
+    return;
+  }
   if (!a.g.periodic[a.axis] && !a.generic) {
     // block size chosen by the host autotuner (a.nt): FP64 128 or 256 threads, FP32 256 or 512
     constexpr int NLO = sizeof(T) == 8 ? 128 : 256;

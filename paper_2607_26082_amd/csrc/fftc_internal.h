@@ -120,6 +120,20 @@ __host__ __device__ inline bool dtt_covered(int ept, const AxisPlan& ap) {
   return true;
 }
 
+// Axis lengths (voxels) with a compile-time FFT
+inline bool dtt_compiled(int n) {
+  return n == 16 || n == 32 || n == 48 || n == 64 || n == 96 || n == 128 || n == 256;
+}
+
+// Matrix passes (fftc_dense.hip): depth of the products for N nodes (a multiple of 8), doubles of one
+// transform matrix, and the LDS stride of an x line (at least the depth, and 4 mod 32: see k_dense)
+__host__ __device__ inline int dense_depth(int N) { return (N + 7) / 8 * 8; }
+__host__ __device__ inline size_t dense_mat_doubles(int N) { return (size_t)((N + 15) / 16) * 16 * dense_depth(N); }
+__host__ __device__ inline int dense_line_stride(int N) {
+  const int k = dense_depth(N);
+  return k + (36 - k % 32) % 32;
+}
+
 template <typename T>
 struct Bufs {
   T* u;        // displacement (also the transform buffer)
@@ -191,6 +205,7 @@ struct DttArgs {
   double thr[3];
   int generic;                 // force the runtime-length kernel
   int nt;                      // threads per block of the compile-time-length kernel
+  const double* mat[3][2];     // per component forward and inverse matrix (matrix passes), or null
   // residual-form (FP32) iteration
   int dst;                     // DST_BUF or DST_UPDATE (x inverse pass: delta and FP64 u update)
   const T* dp2[2];             // p ping-pong buffers (SRC_DELTA, selected by iteration parity)

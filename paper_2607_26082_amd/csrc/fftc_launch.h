@@ -60,6 +60,9 @@ size_t dtt_smem(const AxisPlan& ap);
 template <typename T>
 void launch_dtt(const DttArgs<T>& a, int ept, hipStream_t s);
 template <typename T>
+void launch_dense(const DttArgs<T>& a, hipStream_t s);
+void launch_dense_mats(int type, int n, int N, double* fwd, double* inv, hipStream_t s);
+template <typename T>
 void launch_proj(const Geo& g, T* u, const WeakDev& w, const ContactDev& ct, const StrongDev& sd, DevState* st,
                  int advance, int force, hipStream_t s);
 template <typename T>
