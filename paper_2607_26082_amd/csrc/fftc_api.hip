@@ -535,7 +535,7 @@ struct StageTimer {
 int inc_period(const fftc_problem* h) {
   if (!h->delta_mode || h->fs || h->has_sphere || h->cfg.anchor_every <= 0) return 0;
   if (h->g.sing[0] || h->g.sing[1] || h->g.sing[2] || weak_dev(const_cast<fftc_problem*>(h)).m > 0) return 0;
-  if (residual_tiles(h->g, false).tx <= 0) return 0;
+  if (residual_tiles(h->g, false, false).tx <= 0) return 0;
   return h->cfg.anchor_every;
 }
 
@@ -1568,8 +1568,9 @@ int bind_impl(fftc_h h, void* ws, size_t bytes, void* stream, bool tune, bool ma
     hipEventDestroy(e1);
   }
   // occupancy queries of the residual pass instances, outside any capture
-  (void)residual_tiles(h->g, false);
-  (void)residual_tiles(h->g, true);
+  (void)residual_tiles(h->g, false, false);
+  (void)residual_tiles(h->g, true, false);
+  (void)residual_tiles(h->g, false, true);
   (void)residual_tiles_fp64(h->g, false);
   (void)residual_tiles_fp64(h->g, true);
   if (h->nblk_res >= 8) h->nblk_res -= h->nblk_res % 8;   // whole slabs per XCD
@@ -2007,7 +2008,7 @@ int fftc_stage_residual_form(fftc_h h, const double* u_dev, const double* delta_
   if (!h->bound || !h->stiff_set) return fail(h, FFTC_E_STATE, "workspace and stiffness must be set");
   if (h->precision != FFTC_FP32) return fail(h, FFTC_E_UNSUPPORTED, "the residual form is the FP32 iteration");
   if (pass_kind == 2 && (h->fs || h->has_sphere || h->g.sing[0] || h->g.sing[1] || h->g.sing[2] ||
-                         residual_tiles(h->g, false).tx <= 0))
+                         residual_tiles(h->g, false, false).tx <= 0))
     return fail(h, FFTC_E_UNSUPPORTED, "the incremental pass is for tiled small-strain problems without obstacle "
                                        "or singular modes");
   const double* in[5] = {u_dev, delta_dev, e_dev, pprev_dev, rprev_dev};

@@ -8,37 +8,51 @@ namespace fftc {
 // ---------------------------------------------------------------------------
 // small helpers
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+// v moved by a DPP lane pattern (within rows of 16 lanes)
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// Adds the columns of a table of per-block partials (P columns of nrow values, column q at
-// q * ld) into acc[0..P): thread t takes rows t, t + blockDim.x, t + 2 blockDim.x, ... in that
-// order (the fixed order the solver's reductions have).  Consecutive lanes read consecutive
-// rows, and four rows of every column are loaded before any is added, so their loads are in
-// flight together.
-template <int P, int NV>
-__device__ __forceinline__ void sum_cols(const double* __restrict__ tab, long long ld, long long nrow,
-                                         double (&acc)[NV]) {
-  static_assert(P <= NV, "more columns than accumulators");
-  constexpr int U = 4;
-  const long long bd = blockDim.x;
-  for (long long b0 = threadIdx.x; b0 < nrow; b0 += U * bd) {
-    double v[U][P];
+// Sum over the 64 lanes, in every lane (all must be active).  Rows of 16 by DPP moves, then the four
+// rows through the scalar unit: no LDS traffic (six shuffles of a double are twelve LDS
+// permutes, and the block sums at the end of every pass run two to fourteen of them).
+__device__ __forceinline__ double wave_sum(double v) {
+  v += dpp_move<0x140>(v);   // mirrored in the row
+  v += dpp_move<0x141>(v);   // mirrored in halves of a row
+  v += dpp_move<0x4e>(v);    // lane xor 2
+  v += dpp_move<0xb1>(v);    // lane xor 1
+  return (lane_value(v, 0) + lane_value(v, 32)) + (lane_value(v, 16) + lane_value(v, 48));
+}
+
+// Sums of the columns of a table of per-block partials (ncol columns of nrow values, column q at
+// q * ld) into out[0..ncol) in LDS: wave w of the block takes columns w, w + waves, ..., lane l
+// rows l, l + 64, ... in that order, eight loads in flight.  Ends with a barrier.
+__device__ __forceinline__ void col_sums(const double* __restrict__ tab, long long ld, int nrow, int ncol,
+                                         double* out) {
+  const int lane = threadIdx.x & 63, waves = (int)blockDim.x >> 6;
+  for (int q = (int)threadIdx.x >> 6; q < ncol; q += waves) {
+    const double* col = tab + q * ld;
+    double s = 0.0;
+    for (int b0 = lane; b0 < nrow; b0 += 64 * 8) {
+      double v[8];
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const long long b = b0 + k * bd;
+      for (int k = 0; k < 8; ++k) v[k] = b0 + 64 * k < nrow ? col[b0 + 64 * k] : 0.0;
 #pragma unroll
-      for (int q = 0; q < P; ++q) v[k][q] = b < nrow ? tab[q * ld + b] : 0.0;
+      for (int k = 0; k < 8; ++k) s += v[k];
     }
-#pragma unroll
-    for (int k = 0; k < U; ++k)
-      if (b0 + k * bd < nrow)
-#pragma unroll
-        for (int q = 0; q < P; ++q) acc[q] += v[k][q];
+    s = wave_sum(s);
+    if (lane == 0) out[q] = s;
   }
+  __syncthreads();
 }
 
 // Gaussian elimination with partial pivoting on the augmented N x (N + 1) system G, solution in

@@ -18,6 +18,7 @@ constexpr int kPartStrideD = 14;     // residual-form pass: + 6 singular-mode su
 // Per-block partial sums are stored by column: value q of block b at q * kPartRows + b, so that
 // the one-block kernels that add them up read consecutive blocks on consecutive lanes.
 constexpr int kPartRows = 2048;      // most blocks of a launch that leaves partial sums
+constexpr int kCtlBlock = 512;       // threads of the control step
 constexpr int kMaxSets = 64;
 
 // node mask bits

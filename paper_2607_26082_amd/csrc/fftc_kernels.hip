@@ -396,10 +396,11 @@ __device__ __forceinline__ unsigned active_bytes(unsigned c, unsigned v) {
 constexpr int kStallWindow = 100;
 constexpr double kStallCap = 1e-2;
 
-__global__ __launch_bounds__(kBlock) void k_control(DevState* st, const double* __restrict__ part, int nblk,
-                                                    const double* __restrict__ wpart, long long nweak, ContactDev ct,
-                                                    int pstride) {
-  __shared__ double sh[kPartStrideD * 16];
+// ncol: columns the residual pass left (2 norms; 8 with the mean stress; 14 with the singular modes)
+__global__ __launch_bounds__(kCtlBlock) void k_control(DevState* st, const double* __restrict__ part, int nblk,
+                                                       const double* __restrict__ wpart, int nweak, ContactDev ct,
+                                                       int ncol) {
+  __shared__ double acc[kPartStrideD + 1];   // the columns' sums, then that of the relations
   __shared__ int flags[4];
   __shared__ int decide, s_done, changed;
   if (st->done) return;
@@ -415,16 +416,6 @@ __global__ __launch_bounds__(kBlock) void k_control(DevState* st, const double* 
   // such a pass never ends the solve (the exit test is taken on a pass from u)
   const bool inc = res_pass(st) == PASS_INC;
   const double sn_kept = st->snorm2;
-  double acc[kPartStrideD];
-#pragma unroll
-  for (int q = 0; q < kPartStrideD; ++q) acc[q] = 0.0;
-  if (pstride == kPartStrideD) sum_cols<kPartStrideD>(part, kPartRows, nblk, acc);
-  else sum_cols<kPartStride>(part, kPartRows, nblk, acc);
-  {
-    double w0[1] = {acc[0]};
-    sum_cols<1>(wpart, 0, nweak, w0);
-    acc[0] = w0[0];
-  }
   // contact: compare V with the previous iteration, test emptiness (read before the block
   // sum so that these loads overlap it)
   int differ = 0, nonempty = 0;
@@ -452,18 +443,20 @@ __global__ __launch_bounds__(kBlock) void k_control(DevState* st, const double* 
     }
   }
   if (threadIdx.x == 0) flags[0] = flags[1] = 0;
-  block_sum<kPartStrideD>(acc, sh);   // ends with a barrier
+  if (nweak > 0) col_sums(wpart, 0, nweak, 1, acc + kPartStrideD);
+  col_sums(part, kPartRows, nblk, ncol, acc);   // ends with a barrier
   if (ct.on) {
     if (differ) atomicOr(&flags[0], 1);
     if (nonempty) atomicOr(&flags[1], 1);
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    const double pn = acc[0], sn = inc ? sn_kept : acc[1];
+    const double pn = acc[0] + (nweak > 0 ? acc[kPartStrideD] : 0.0), sn = inc ? sn_kept : acc[1];
     st->pnorm2 = pn;
     st->snorm2 = sn;
-    for (int q = 0; q < 6; ++q) st->ms[q] = acc[2 + q];
-    if (pstride > kPartStride)
+    if (ncol >= kPartStride)
+      for (int q = 0; q < 6; ++q) st->ms[q] = acc[2 + q];
+    if (ncol > kPartStride)
       for (int q = 0; q < 6; ++q) st->sing[q] = acc[8 + q];
     double res;
     if (pn == 0.0) res = 0.0;
@@ -610,13 +603,9 @@ __global__ __launch_bounds__(kBlock) void k_anderson_r(Bufs<T> B, long long n3, 
 
 // alpha = argmin |sum a_k R_k|, sum a_k = 1, from the regularised FP64 Gram matrix.
 __global__ __launch_bounds__(kBlock) void k_alpha(DevState* st, const double* __restrict__ gpart, int nblk) {
-  __shared__ double sh[10 * 16];
+  __shared__ double acc[10];
   if (st->done || !st->accel) return;
-  double acc[10];
-#pragma unroll
-  for (int q = 0; q < 10; ++q) acc[q] = 0.0;
-  sum_cols<10>(gpart, kPartRows, nblk, acc);
-  block_sum<10>(acc, sh);
+  col_sums(gpart, kPartRows, nblk, 10, acc);
   if (threadIdx.x != 0) return;
   double G[4][5];
   int t = 0;
@@ -1101,8 +1090,8 @@ void launch_weak(const Geo& g, const Bufs<T>& B, const WeakDev& w, DevState* st,
 }
 
 void launch_control(DevState* st, const double* part, int nblk, const double* wpart, long long nweak,
-                    const ContactDev& ct, int pstride, hipStream_t s) {
-  hipLaunchKernelGGL(k_control, dim3(1), dim3(kBlock), 0, s, st, part, nblk, wpart, nweak, ct, pstride);
+                    const ContactDev& ct, int ncol, hipStream_t s) {
+  hipLaunchKernelGGL(k_control, dim3(1), dim3(kCtlBlock), 0, s, st, part, nblk, wpart, (int)nweak, ct, ncol);
 }
 
 template <typename T>

@@ -10,7 +10,7 @@ void launch_residual(const Geo& g, const Bufs<T>& B, const ContactDev& ct, DevSt
 template <typename T>
 void launch_weak(const Geo& g, const Bufs<T>& B, const WeakDev& w, DevState* st, int force, hipStream_t s);
 void launch_control(DevState* st, const double* part, int nblk, const double* wpart, long long nweak,
-                    const ContactDev& ct, int pstride, hipStream_t s);
+                    const ContactDev& ct, int ncol, hipStream_t s);
 // Residual-form iteration, first half: the residual pass (returns the number of block
 // partial rows it wrote), then the average relations and the control step over those rows.
 // refine: the solve may take the FP64-stress pass (once the state's refinement flag is set);
@@ -25,7 +25,7 @@ void launch_delta_control(const Geo& g, const DeltaBufs<T>& D, const ContactDev&
 // Tile grid of the tiled residual pass on the current device.  Its first call on a device
 // queries the kernel's occupancy, which must not happen under stream capture: call it once
 // outside capture (the workspace binding does) before capturing iterations.
-TileGrid residual_tiles(const Geo& g, bool inc);
+TileGrid residual_tiles(const Geo& g, bool gen, bool inc);
 TileGrid residual_tiles_fp64(const Geo& g, bool gen);
 template <typename T>
 void launch_delta_anderson(const DeltaBufs<T>& D, long long n3, DevState* st, double* gpart, int nblk, hipStream_t s);

@@ -2,10 +2,12 @@
 #include "fftc_internal.h"
 #include "fftc_launch.h"
 #include "fftc_common.h"
+#include "fftc_march.h"
 
 #include <math.h>
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 namespace fftc {
 
@@ -166,8 +168,7 @@ __device__ __forceinline__ double sing_weight(const Geo& g, const int xyz[3]) {
 template <typename T>
 struct TailIn {
   uint8_t m;
-  T cw;   // 1 after an accelerating iteration, else 0 (c is then p_{i-1}, read in its place)
-  T c[3], pp[3];
+  T c[3], pp[3];   // c after an accelerating iteration, else p_{i-1} in its place (the tail weighs it 0)
 };
 
 template <typename T>
@@ -175,27 +176,23 @@ __device__ __forceinline__ void tail_load(const DeltaBufs<T>& D, long long Nn, b
                                           const T* pp, long long node, TailIn<T>& t) {
   t.m = D.mask[node];
   // a uniform choice of source (no branch around the loads): after a plain iteration c is 0
-  // and the second load of p_{i-1} is served by the cache.  The pass from u applies cw in
-  // the tail, so its loads stay in flight over the layer's stresses (applied here, the pass
-  // took 0.82 instead of 0.72 ms at 256^3); the incremental pass, which fetches these inputs
-  // one step ahead, applies it here (0.53 against 0.55 ms per iteration, measured).
+  // and the second load of p_{i-1} is served by the cache.  The weight is applied in the tail, so
+  // the loads stay in flight over the layer's stresses.
   const T* cs = ecomb ? D.e : pp;
-  t.cw = ecomb ? T(1) : T(0);
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     t.c[c] = T(0);
     t.pp[c] = T(0);
     if (kd_used || inc) t.pp[c] = pp[c * Nn + node];
-    if (kd_used) t.c[c] = inc ? t.cw * cs[c * Nn + node] : cs[c * Nn + node];
+    if (kd_used) t.c[c] = cs[c * Nn + node];
   }
-  if (inc) t.cw = T(1);
 }
 
 // GEN = false: no rigid obstacle and no singular modes (both checked by the launcher).
 template <typename T, bool GEN, bool INC = false>
 __device__ __forceinline__ void delta_tail(const Geo& g, const DeltaBufs<T>& D, const ContactDev& ct, int cur,
                                            bool kd_used, int il, int slot, T* pc, T* Rc, int i, int j, int k,
-                                           long long node, T p[3], const T kd[3], const TailIn<T>& tin,
+                                           long long node, T p[3], const T kd[3], const TailIn<T>& tin, T cw,
                                            double* acc) {
   static_assert(!(GEN && INC), "the incremental pass has no contact or singular modes");
   const long long Nn = g.Nn;
@@ -255,7 +252,7 @@ __device__ __forceinline__ void delta_tail(const Geo& g, const DeltaBufs<T>& D, 
       // symmetric image; the transforms drop these entries, but they stay in the Gram matrix
       // of the differences (measured: zeroing them makes the FP32 least squares less robust).
       const T y = dp[c] + kd[c];
-      Rc[e] = y + tin.cw * tin.c[c];
+      Rc[e] = y + cw * tin.c[c];
       if (il >= 2) D.dY[slot][e] = y;
     }
   }
@@ -296,7 +293,7 @@ __global__ __launch_bounds__(kBlock) void k_residual_d(Geo g, DeltaBufs<T> D, Co
     if (kd_used) stencil_k0<T>(g, D.delta, i, j, k, kd);
     TailIn<T> tin;
     tail_load<T>(D, Nn, kd_used, false, ecomb, pp, node, tin);
-    delta_tail<T, true>(g, D, ct, cur, kd_used, il, slot, pc, Rc, i, j, k, node, p, kd, tin, acc);
+    delta_tail<T, true>(g, D, ct, cur, kd_used, il, slot, pc, Rc, i, j, k, node, p, kd, tin, ecomb ? T(1) : T(0), acc);
   }
   block_sum<kPartStrideD>(acc, sh);
   if (threadIdx.x == 0)
@@ -304,42 +301,35 @@ __global__ __launch_bounds__(kBlock) void k_residual_d(Geo g, DeltaBufs<T> D, Co
     for (int q = 0; q < kPartStrideD; ++q) part[q * kPartRows + blockIdx.x] = acc[q];
 }
 
-// ---------------------------------------------------------------------------
-// The same residual pass, tiled: a block owns a kTX x kTY column of nodes and marches
-// along z over a segment of node planes.  Node planes of u (FP64) and of delta (with the
-// stencil's mirrored / periodic halo) sit in LDS with a one-node halo; the stresses of the
-// two tetrahedra of every voxel of a layer are formed once per block (differences of u
-// taken in FP64 against the voxel's corner 000, then rounded) and serve the two node
-// planes that bound the layer.  Every voxel's stress-norm and mean-stress terms are
-// counted by the one block whose node column and segment contain its corner 000.
-// ---------------------------------------------------------------------------
-constexpr int kTX = 31, kTY = 7;                // 217 nodes; 32 x 8 = 256 voxels per layer
-constexpr int kHX = kTX + 2, kHY = kTY + 2;   // node tile with halo: x0-1 .. x0+kTX
-constexpr int kVX = kTX + 1, kVY = kTY + 1;   // voxels x0-1 .. x0+kTX-1
-constexpr int kPlane = 3 * kHY * kHX;         // values of one staged node plane
-constexpr int kPR = (kPlane + 255) / 256;     // of them per thread
+// slot of node plane pz (>= -1) in a ring of three
+__device__ __forceinline__ int ring3(int pz) { return (pz + 3) % 3; }
 
-// slot of node plane p in the four-plane ring of delta planes (p may be -1)
-__device__ __forceinline__ int ring4(int p) { return p & 3; }
-
-// INC: the incremental pass (small strain, no contact or singular modes): the stresses are
-// those of delta_i, formed in T from the delta planes, and p_i = p_{i-1} + their divergence
-// term; u is not read and no stress norm is formed (the control keeps the last full pass's).
-// The small-strain pass with contact or singular modes (GEN, T stresses) is held to three
-// waves per SIMD, the residency the tile grid assumes (it needed one register granule more:
-// two blocks per CU ran the grid in two rounds).
+// The tiled residual pass (see fftc_march.h).  Fields: u (FP64, passes from u) gives the stresses,
+// delta the reference-medium term K0 delta and, in the incremental pass (INC: small strain, no
+// contact or singular modes), the stresses: p_i = p_{i-1} + their divergence term; u is then not
+// read and no stress norm is formed (the control keeps the last full pass's).
+//
+// K0 delta at a node is a stencil over three planes; with A = st0 delta + st1 (its four in-plane
+// diagonal neighbours) and S = st2 (x neighbours) + st3 (y neighbours) formed once per plane it is
+// A_z + S_{z-1} + S_{z+1}: 9 LDS reads per component and step, four of them the voxel's corners.
+//
+// Bound by LDS and VALU issue and the latency of a step about equally: at 256^3 the incremental pass
+// moves 1.38 GB in 445 us, 3.1 TB/s (527 us with every node forming its 24 corner forces from
+// stresses passed through LDS, two barriers per step); at 128^3 60 us (89), at 64^3 26 us (36).
+// Registers set the blocks per CU: held to four, the incremental pass spills 6 of them and takes
+// 70 us at 128^3; at three nothing spills, which the passes with T stresses are held to as well
+// (those with contact or singular modes would spill).
 template <typename T, bool FS, bool GEN, typename TS, bool INC = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((GEN && !FS && sizeof(TS) == 4) ? 3 : 1)))
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(!GEN && sizeof(TS) == 4 ? 3 : 1)))
 void k_residual_dt(Geo g, DeltaBufs<T> D, ContactDev ct, DevState* st, double* __restrict__ part, TileGrid tg) {
   static_assert(!INC || (!FS && !GEN && sizeof(TS) == sizeof(T)), "incremental pass: small strain, T stresses");
-  constexpr int NQ = FS ? 9 : 6;      // stored stress components per tetrahedron (PK1: all nine)
-  __shared__ double su_raw[INC ? 1 : 2 * 3 * kHY * kHX];
-  double (*su)[3][kHY][kHX] = reinterpret_cast<double (*)[3][kHY][kHX]>(su_raw);
-  __shared__ T sdl[4][3][kHY][kHX];
-  __shared__ TS ss[2][2 * NQ][kVY][kVX];   // stress component q of the voxels of a layer (in TS)
-  // the final block sum reuses the stress buffer (block_sum starts with a barrier)
-  static_assert(sizeof(ss) >= sizeof(double) * kPartStrideD * 16, "block-sum scratch");
-  double* sh = reinterpret_cast<double*>(&ss[0][0][0][0]);
+  using TU = std::conditional_t<INC, T, double>;
+  constexpr int NS = GEN ? kPartStrideD : 2;   // partial sums (INC leaves the second 0)
+  __shared__ double su[INC ? 1 : 2][INC ? 1 : 3][INC ? 1 : kHY][INC ? 1 : kHX];
+  __shared__ T sdl[3][3][kHY][kHX];   // three planes: read in both halves of a step
+  __shared__ TS sx[2][9][kVY][kVX];   // exchanged corner forces
+  __shared__ double sh[NS * 16];
   if (st->done || res_pass(st) != (INC ? PASS_INC : (sizeof(TS) == 8 ? PASS_U64 : PASS_U))) return;
   const int tid = threadIdx.x;
   // contiguous ranges of tiles per XCD (blocks go to the 8 XCDs round-robin), so that
@@ -356,7 +346,7 @@ void k_residual_dt(Geo g, DeltaBufs<T> D, ContactDev ct, DevState* st, double* _
   const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
   const int zb = bz * tg.seg;
   const int ze = min(zb + tg.seg, Nz);
-  const int Nn = (int)g.Nn;
+  const int NxNy = Nx * Ny;
   const int cur = ct.on ? st->vpar : 0;
   const int il = st->i_local, par = st->it & 1, acvp = (st->acv == 2), ecomb = st->accel_ok;
   const int slot = (il + 1) % 3;
@@ -365,275 +355,191 @@ void k_residual_dt(Geo g, DeltaBufs<T> D, ContactDev ct, DevState* st, double* _
   T* pc = D.p[par];
   const T* pp = D.p[par ^ 1];
   T* Rc = D.R[il & 3];
-  double acc[kPartStrideD];
+  double acc[NS];
 #pragma unroll
-  for (int q = 0; q < kPartStrideD; ++q) acc[q] = 0.0;
+  for (int q = 0; q < NS; ++q) acc[q] = 0.0;
 
-  // Node planes are fetched into registers one step ahead and committed to LDS the next
-  // step.  u: su[pz & 1], nodes outside the grid read as 0 (no voxel uses them); delta:
-  // sdl[pz mod 4] with the stencil's halo (mirror or periodic image).
+  int off[kPR];
+  plane_offsets(g, x0, y0, tid, off);
   double ru[INC ? 1 : kPR];
   T rd[kPR];
   auto fetch = [&](int pz) {
-    int gz = pz;
-    bool okz = true;
-    if (g.periodic[2]) gz = (pz + Nz) % Nz;
-    else okz = pz >= 0 && pz < Nz;
     const int mz = mirror_coord(g, pz, 2);
-    const bool okm = mz >= 0 && mz < Nz;
+    const bool okz = mz >= 0 && mz < Nz;
 #pragma unroll
     for (int r = 0; r < kPR; ++r) {
-      const int e = tid + 256 * r;
-      if constexpr (!INC) ru[r] = 0.0;
+      const bool ok = okz && off[r] >= 0;
+      const int a = off[r] + NxNy * mz;
+      if constexpr (!INC) ru[r] = ok ? D.u[a] : 0.0;
       rd[r] = T(0);
-      if (e < kPlane) {
-        const int c = e / (kHY * kHX), q = e - c * (kHY * kHX);
-        const int hy = q / kHX, hx = q - hy * kHX;
-        int gx = x0 - 1 + hx, gy = y0 - 1 + hy;
-        bool ok = okz;
-        if (g.periodic[0]) gx = (gx + Nx) % Nx;
-        else ok = ok && gx >= 0 && gx < Nx;
-        if (g.periodic[1]) gy = (gy + Ny) % Ny;
-        else ok = ok && gy >= 0 && gy < Ny;
-        if constexpr (!INC)
-          if (ok) ru[r] = D.u[c * Nn + gx + Nx * (gy + Ny * gz)];
-        if (dl) {
-          const int mx = mirror_coord(g, x0 - 1 + hx, 0), my = mirror_coord(g, y0 - 1 + hy, 1);
-          if (okm && mx >= 0 && mx < Nx && my >= 0 && my < Ny) rd[r] = D.delta[c * Nn + mx + Nx * (my + Ny * mz)];
-        }
-      }
+      if (dl && ok) rd[r] = D.delta[a];
     }
   };
   auto commit = [&](int pz) {
-    double* du = INC ? nullptr : &su[pz & 1][0][0][0];
-    T* dd = &sdl[ring4(pz)][0][0][0];
 #pragma unroll
     for (int r = 0; r < kPR; ++r) {
       const int e = tid + 256 * r;
       if (e < kPlane) {
-        if constexpr (!INC) du[e] = ru[r];
-        if (dl) dd[e] = rd[r];
+        if constexpr (!INC) (&su[pz & 1][0][0][0])[e] = ru[r];
+        if (dl) (&sdl[ring3(pz)][0][0][0])[e] = rd[r];
       }
     }
   };
-  // Every thread owns one voxel of a layer (kVX * kVY = 256): local (vlx, vly).
-  const int vly = tid / kVX, vlx = tid - (tid / kVX) * kVX;
-  const int vux = x0 - 1 + vlx, vuy = y0 - 1 + vly;   // unwrapped voxel coordinates
-  int vxw = vux, vyw = vuy;
+  const int lx = tid & (kVX - 1), ly = tid / kVX;
+  const int i = x0 - 1 + lx, j = y0 - 1 + ly;   // the thread's node, and its voxel's corner 000
+  const bool nact = lx >= 1 && ly >= 1 && i < Nx && j < Ny;
+  int vx = i, vy = j;
   bool vok = true;
-  if (g.periodic[0]) vxw = (vux + nx) % nx;
-  else vok = vux >= 0 && vux < nx;
-  if (g.periodic[1]) vyw = (vuy + ny) % ny;
-  else vok = vok && vuy >= 0 && vuy < ny;
-  // Lame values of this thread's voxel in layer lz (fetched one step ahead)
-  auto fetch_lm = [&](int lz, T& l, T& m, bool& ok) {
+  if (g.periodic[0]) vx = (vx + nx) % nx;
+  else vok = vx >= 0 && vx < nx;
+  if (g.periodic[1]) vy = (vy + ny) % ny;
+  else vok = vok && vy >= 0 && vy < ny;
+  const int vxy = vx + nx * vy, nxny = nx * ny;
+  const bool own = !INC && lx >= 1 && ly >= 1 && i < nx && j < ny;   // voxel whose norm this block counts
+  // Lame values of the thread's voxel in layer lz; 0 outside the grid
+  auto fetch_lm = [&](int lz, T& l, T& m) {
+    bool ok = vok;
     int vz = lz;
-    ok = vok;
     if (g.periodic[2]) vz = (lz + nz) % nz;
     else ok = ok && lz >= 0 && lz < nz;
-    l = T(0);
-    m = T(0);
+    l = m = T(0);
     if (ok) {
-      const int vid = vxw + nx * (vyw + ny * vz);
-      l = D.lam[vid];
-      m = D.mu[vid];
+      l = D.lam[vxy + nxny * vz];
+      m = D.mu[vxy + nxny * vz];
     }
   };
-  // voxel layer lz (between node planes lz and lz+1, held in su[lz & 1] and su[(lz+1) & 1])
-  auto layer = [&](int lz, bool own_z, T l, T m, bool ok) {
-    const int lo = lz & 1, hi = (lz + 1) & 1;
-    {
-      const int ly = vly, lx = vlx;
-      TS (*out)[kVY][kVX] = ss[lz & 1];
-      const int ux = vux, uy = vuy;
-      if (!ok) {
+  const NodeXY nxy = node_xy(g, i, j);
+  const int wx = lx >= 1 ? lx - 1 : 0, sy = ly >= 1 ? ly - 1 : 0;   // (unused values of the halo threads)
+  // corners of the thread's voxel in plane pz
+  auto read_corners = [&](int pz, TU (&cn)[4][3]) {
+    const int s = pz & 1, r = ring3(pz);
 #pragma unroll
-        for (int q = 0; q < 2 * NQ; ++q) out[q][ly][lx] = TS(0);
-        return;
-      }
-      const TS lt = (TS)l, mt = (TS)m;
-      TS d[8][3];
+    for (int c = 0; c < 3; ++c) {
       if constexpr (INC) {
-        // differences of delta (T) against the voxel's corner 000
-        const int s0 = ring4(lz), s1 = ring4(lz + 1);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const T ref = sdl[s0][c][ly][lx];
-#pragma unroll
-          for (int cc = 0; cc < 8; ++cc) {
-            const int cx = cc & 1, cy = (cc >> 1) & 1, cz = (cc >> 2) & 1;
-            d[cc][c] = cc == 0 ? TS(0) : (TS)(sdl[cz ? s1 : s0][c][ly + cy][lx + cx] - ref);
-          }
-        }
+        cn[0][c] = sdl[r][c][ly][lx];
+        cn[1][c] = sdl[r][c][ly][lx + 1];
+        cn[2][c] = sdl[r][c][ly + 1][lx];
+        cn[3][c] = sdl[r][c][ly + 1][lx + 1];
       } else {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const double ref = su[lo][c][ly][lx];
-#pragma unroll
-          for (int cc = 0; cc < 8; ++cc) {
-            const int cx = cc & 1, cy = (cc >> 1) & 1, cz = (cc >> 2) & 1;
-            d[cc][c] = cc == 0 ? TS(0) : (TS)(su[cz ? hi : lo][c][ly + cy][lx + cx] - ref);
-          }
-        }
+        cn[0][c] = su[s][c][ly][lx];
+        cn[1][c] = su[s][c][ly][lx + 1];
+        cn[2][c] = su[s][c][ly + 1][lx];
+        cn[3][c] = su[s][c][ly + 1][lx + 1];
       }
-      const bool own = !INC && own_z && ux >= x0 && ux < x0 + kTX && ux < nx && uy >= y0 && uy < y0 + kTY && uy < ny;
-      TS vs = TS(0);
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        TS G[3][3];
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-#pragma unroll
-          for (int q = 0; q < 3; ++q) G[r][q] = TS(0);
-#pragma unroll
-        for (int cc = 0; cc < 8; ++cc) {
-          const int cx = cc & 1, cy = (cc >> 1) & 1, cz = (cc >> 2) & 1;
-          if (((cx + cy + cz) & 1) != t) continue;
-          const TS sx = TS(cx ? 0.5 : -0.5), sy = TS(cy ? 0.5 : -0.5), sz = TS(cz ? 0.5 : -0.5);
-#pragma unroll
-          for (int r = 0; r < 3; ++r) {
-            G[r][0] += sx * d[cc][r];
-            G[r][1] += sy * d[cc][r];
-            G[r][2] += sz * d[cc][r];
-          }
-        }
-        if constexpr (FS) {
-          TS P[3][3];
-          svk_pk1<TS>(G, lt, mt, P);
-#pragma unroll
-          for (int r = 0; r < 3; ++r)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) out[t * 9 + r * 3 + c][ly][lx] = P[r][c];
-          if (own) {
-#pragma unroll
-            for (int r = 0; r < 3; ++r)
-#pragma unroll
-              for (int c = 0; c < 3; ++c) vs += P[r][c] * P[r][c];
-          }
-          continue;
-        }
-        const TS tr = G[0][0] + G[1][1] + G[2][2];
-        const TS s00 = lt * tr + TS(2) * mt * G[0][0];
-        const TS s11 = lt * tr + TS(2) * mt * G[1][1];
-        const TS s22 = lt * tr + TS(2) * mt * G[2][2];
-        const TS s01 = mt * (G[0][1] + G[1][0]);
-        const TS s02 = mt * (G[0][2] + G[2][0]);
-        const TS s12 = mt * (G[1][2] + G[2][1]);
-        out[t * 6 + 0][ly][lx] = s00;
-        out[t * 6 + 1][ly][lx] = s11;
-        out[t * 6 + 2][ly][lx] = s22;
-        out[t * 6 + 3][ly][lx] = s01;
-        out[t * 6 + 4][ly][lx] = s02;
-        out[t * 6 + 5][ly][lx] = s12;
-        // the voxel's two tetrahedra in T, added to the FP64 block sum once per voxel
-        if (own) vs += s00 * s00 + s11 * s11 + s22 * s22 + TS(2) * (s01 * s01 + s02 * s02 + s12 * s12);
-      }
-      if (own) acc[1] += 0.5 * (double)vs;
     }
   };
-  const int nlx = tid % kTX, nly = tid / kTX;
-  const bool nact = tid < kTX * kTY && x0 + nlx < Nx && y0 + nly < Ny;
+  // A and S of K0 delta in plane pz at the thread's node (INC: cn are the plane's corners)
+  auto read_stencil = [&](int pz, const TU (&cn)[4][3], T (&A)[3], T (&S)[3]) {
+    const int r = ring3(pz);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      A[c] = S[c] = T(0);
+      if (!kd_used) continue;
+      const T d0 = INC ? (T)cn[0][c] : sdl[r][c][ly][lx], de = INC ? (T)cn[1][c] : sdl[r][c][ly][lx + 1];
+      const T dn = INC ? (T)cn[2][c] : sdl[r][c][ly + 1][lx], dne = INC ? (T)cn[3][c] : sdl[r][c][ly + 1][lx + 1];
+      const T dw = sdl[r][c][ly][wx], ds = sdl[r][c][sy][lx];
+      const T dsw = sdl[r][c][sy][wx], dse = sdl[r][c][sy][lx + 1], dnw = sdl[r][c][ly + 1][wx];
+      A[c] = T(g.st[c][0]) * d0 + T(g.st[c][1]) * ((dsw + dse) + (dnw + dne));
+      S[c] = T(g.st[c][2]) * (dw + de) + T(g.st[c][3]) * (ds + dn);
+    }
+  };
   TailIn<T> tin;
-  auto nodes = [&](int z) {
-    if (!nact) return;
-    const int lx = nlx, ly = nly;
-    const int i = x0 + lx, j = y0 + ly;
-    TS F[3] = {TS(0), TS(0), TS(0)};
-#pragma unroll
-    for (int a = 0; a < 8; ++a) {
-      const int ax = a & 1, ay = (a >> 1) & 1, az = (a >> 2) & 1;
-      // voxel (i - ax, j - ay, z - az): local voxel (lx + 1 - ax, ly + 1 - ay), layer z - az;
-      // the node is its corner (ax, ay, az), in tetrahedron T1 (even) or T2 (odd)
-      const int q0 = ((ax + ay + az) & 1) * NQ, vy = ly + 1 - ay, vx = lx + 1 - ax;
-      TS (*sv)[kVY][kVX] = ss[(z - az) & 1];
-      const TS bxw = TS(ax ? 0.25 : -0.25), byw = TS(ay ? 0.25 : -0.25), bzw = TS(az ? 0.25 : -0.25);
-      if constexpr (FS) {
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-          F[r] += bxw * sv[q0 + 3 * r][vy][vx] + byw * sv[q0 + 3 * r + 1][vy][vx] + bzw * sv[q0 + 3 * r + 2][vy][vx];
-        continue;
-      }
-      const TS s00 = sv[q0 + 0][vy][vx], s11 = sv[q0 + 1][vy][vx], s22 = sv[q0 + 2][vy][vx];
-      const TS s01 = sv[q0 + 3][vy][vx], s02 = sv[q0 + 4][vy][vx], s12 = sv[q0 + 5][vy][vx];
-      F[0] += bxw * s00 + byw * s01 + bzw * s02;
-      F[1] += bxw * s01 + byw * s11 + bzw * s12;
-      F[2] += bxw * s02 + byw * s12 + bzw * s22;
-    }
-    const int xyz[3] = {i, j, z};
-    const TS w2b = TS(1 << bcount(g, xyz));
-    T p[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) p[c] = is_antisym(g, c, xyz) ? T(0) : (T)(-w2b * F[c]);
-    T kd[3] = {T(0), T(0), T(0)};
-    if (kd_used) {
-      const int zm = ring4(z - 1), z0 = ring4(z), zp = ring4(z + 1);
-      const int hx = lx + 1, hy = ly + 1;
-      // one component at a time: keeps the 13 LDS reads of a component, not all 39, in
-      // flight (194 -> 155 VGPRs, three waves per SIMD instead of two)
-#pragma unroll 1
-      for (int c = 0; c < 3; ++c) {
-        const T sxy = sdl[z0][c][hy - 1][hx - 1] + sdl[z0][c][hy - 1][hx + 1] + sdl[z0][c][hy + 1][hx - 1] +
-                      sdl[z0][c][hy + 1][hx + 1];
-        const T sxz = sdl[zm][c][hy][hx - 1] + sdl[zm][c][hy][hx + 1] + sdl[zp][c][hy][hx - 1] +
-                      sdl[zp][c][hy][hx + 1];
-        const T syz = sdl[zm][c][hy - 1][hx] + sdl[zm][c][hy + 1][hx] + sdl[zp][c][hy - 1][hx] +
-                      sdl[zp][c][hy + 1][hx];
-        kd[c] = T(g.st[c][0]) * sdl[z0][c][hy][hx] + T(g.st[c][1]) * sxy + T(g.st[c][2]) * sxz +
-                T(g.st[c][3]) * syz;
-      }
-    }
-    const long long node = (long long)i + (long long)Nx * ((long long)j + (long long)Ny * z);
-    delta_tail<T, GEN, INC>(g, D, ct, cur, kd_used, il, slot, pc, Rc, i, j, z, node, p, kd, tin, acc);
+  auto tail_at = [&](int z, TailIn<T>& t) {
+    tail_load<T>(D, g.Nn, kd_used, INC, ecomb, pp, (long long)i + (long long)Nx * j + (long long)NxNy * z, t);
   };
 
-  T lcur, mcur, lnext, mnext;
-  bool okcur, oknext;
+  T lam, mu;
+  TU lo[4][3];   // corners of the lower plane of the current layer
+  TS fu[4][3];   // forces of the layer below on its upper corners
+  T Kz[3], S0[3];   // A_z + S_{z-1}, S_z
   fetch(zb - 1);
   commit(zb - 1);
   fetch(zb);
   commit(zb);
   fetch(zb + 1);
-  fetch_lm(zb - 1, lcur, mcur, okcur);
-  fetch_lm(zb, lnext, mnext, oknext);
-  // the incremental pass (fewer registers) fetches the tail inputs one step ahead
-  TailIn<T> tnext;
-  auto tail_at = [&](int z, TailIn<T>& t) {
-    const long long node = (long long)(x0 + nlx) + (long long)Nx * ((long long)(y0 + nly) + (long long)Ny * z);
-    tail_load<T>(D, g.Nn, kd_used, INC, ecomb, pp, node, t);
-  };
-  if (INC && nact) tail_at(zb, tnext);
+  fetch_lm(zb - 1, lam, mu);
+  if (nact) tail_at(zb, tin);
   __syncthreads();
-  layer(zb - 1, false, lcur, mcur, okcur);
-  __syncthreads();
-  // Per step, plane z + 1 is committed with no barrier before it: its u slot was last read
-  // by layer(z - 1), and its delta slot (four-plane ring) by nodes(z - 2), both before the
-  // barrier that follows layer(z - 1).  The stress slot written by layer(z) was last read by
-  // nodes(z - 1), which precedes the barrier before layer(z).
-  for (int z = zb; z < ze; ++z) {
-    commit(z + 1);
-    if (z + 2 <= ze) fetch(z + 2);
-    lcur = lnext;
-    mcur = mnext;
-    okcur = oknext;
-    if (z + 1 < ze) fetch_lm(z + 1, lnext, mnext, oknext);
-    if constexpr (INC) {
-      tin = tnext;
-      if (nact && z + 1 < ze) tail_at(z + 1, tnext);
-    } else {
-      if (nact) tail_at(z, tin);
-    }
-    __syncthreads();
-    layer(z, true, lcur, mcur, okcur);
-    __syncthreads();
-    nodes(z);
+  {
+    TU up[4][3];
+    TS fl[4][3], vs = TS(0), ms[6];
+    read_corners(zb - 1, lo);
+    read_corners(zb, up);
+    T A[3], S[3];
+    read_stencil(zb - 1, lo, A, S);
+    read_stencil(zb, up, A, S0);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) Kz[c] = A[c] + S[c];
+    voxel_forces<TU, TS, FS, false>(lo, up, (TS)lam, (TS)mu, fl, fu, vs, ms);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) lo[k][c] = up[k][c];
   }
-  block_sum<kPartStrideD>(acc, sh);
+  fetch_lm(zb, lam, mu);
+  __syncthreads();
+  commit(zb + 1);
+  if (zb + 1 < ze) fetch(zb + 2);
+  __syncthreads();
+  for (int z = zb; z < ze; ++z) {
+    TS (*ex)[kVY][kVX] = sx[z & 1];
+    TS F0[3];   // forces on the thread's own corner (0, 0)
+    {
+      TU up[4][3];
+      TS fl[4][3], fn[4][3];
+      TS vs = TS(0), ms[6] = {TS(0), TS(0), TS(0), TS(0), TS(0), TS(0)};
+      read_corners(z + 1, up);
+      voxel_forces<TU, TS, FS, !INC>(lo, up, (TS)lam, (TS)mu, fl, fn, vs, ms);
+      if (own) acc[1] += 8.0 * (double)vs;   // (1/2) sigma : sigma
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        F0[c] = fl[0][c] + fu[0][c];
+#pragma unroll
+        for (int k = 1; k < 4; ++k) ex[3 * (k - 1) + c][ly][lx] = fl[k][c] + fu[k][c];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          fu[k][c] = fn[k][c];
+          lo[k][c] = up[k][c];
+        }
+      }
+    }
+    // the next layer's and the next node's inputs are requested as soon as their registers are free
+    if (z + 1 < ze) {
+      fetch_lm(z + 1, lam, mu);
+      commit(z + 2);
+    }
+    if (z + 2 < ze) fetch(z + 3);
+    __syncthreads();
+    T A1[3], S1[3];
+    read_stencil(z + 1, lo, A1, S1);
+    if (nact) {
+      const NodeXY nz_ = node_z(g, z);
+      const TS w2b = TS(1 << (nxy.b + nz_.b));
+      const int anti = nxy.anti | nz_.anti;
+      T p[3], kd[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const TS F = (F0[c] + ex[c][ly][lx - 1]) + (ex[3 + c][ly - 1][lx] + ex[6 + c][ly - 1][lx - 1]);
+        p[c] = ((anti >> c) & 1) ? T(0) : (T)(-w2b * F);
+        kd[c] = Kz[c] + S1[c];
+      }
+      const long long node = (long long)i + (long long)Nx * j + (long long)NxNy * z;
+      delta_tail<T, GEN, INC>(g, D, ct, cur, kd_used, il, slot, pc, Rc, i, j, z, node, p, kd, tin, ecomb ? T(1) : T(0), acc);
+      if (z + 1 < ze) tail_at(z + 1, tin);
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      Kz[c] = A1[c] + S0[c];
+      S0[c] = S1[c];
+    }
+  }
+  block_sum<NS>(acc, sh);
   if (threadIdx.x == 0)
 #pragma unroll
-    for (int q = 0; q < kPartStrideD; ++q) part[q * kPartRows + blockIdx.x] = acc[q];
+    for (int q = 0; q < NS; ++q) part[q * kPartRows + blockIdx.x] = acc[q];
   // rows the control sums beyond this grid (another instance's larger grid): cleared
   if (blockIdx.x == 0)
-    for (int q = 0; q < kPartStrideD; ++q)
+    for (int q = 0; q < NS; ++q)
       for (int r = (int)gridDim.x + tid; r < tg.rows; r += 256) part[q * kPartRows + r] = 0.0;
 }
 
@@ -781,38 +687,48 @@ __global__ __launch_bounds__(kBlock) void k_gram3(DeltaBufs<T> D, long long n3, 
   __shared__ double sh[9 * 16];
   if (st->done || !st->accel) return;
   const int il = st->i_local;
-  const T* Ri = D.R[il & 3];
-  const T *Ra[3], *Rb[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const int j = il - k, slot = (j + 1) % 3;
-    Ra[slot] = D.R[j & 3];
-    Rb[slot] = D.R[(j + 3) & 3];
-  }
+  // d_k = R_{i-k} - R_{i-k-1}, k = 0, 1, 2: four fields, each read once
+  const T *r0 = D.R[il & 3], *r1 = D.R[(il + 3) & 3], *r2 = D.R[(il + 2) & 3], *r3 = D.R[(il + 1) & 3];
   double acc[9];
 #pragma unroll
   for (int q = 0; q < 9; ++q) acc[q] = 0.0;
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < n3; e += (long long)gridDim.x * blockDim.x) {
-    const T d0 = Ra[0][e] - Rb[0][e], d1 = Ra[1][e] - Rb[1][e], d2 = Ra[2][e] - Rb[2][e];
-    const double a0 = d0, a1 = d1, a2 = d2, r = Ri[e];
-    acc[0] += a0 * a0; acc[1] += a0 * a1; acc[2] += a0 * a2;
-    acc[3] += a1 * a1; acc[4] += a1 * a2; acc[5] += a2 * a2;
-    acc[6] += a0 * r; acc[7] += a1 * r; acc[8] += a2 * r;
+  auto add = [&](T a, T b, T c, T d) {
+    const double r = a, d0 = (T)(a - b), d1 = (T)(b - c), d2 = (T)(c - d);
+    acc[0] += d0 * d0; acc[1] += d0 * d1; acc[2] += d0 * d2;
+    acc[3] += d1 * d1; acc[4] += d1 * d2; acc[5] += d2 * d2;
+    acc[6] += d0 * r; acc[7] += d1 * r; acc[8] += d2 * r;
+  };
+  typedef T T4 __attribute__((ext_vector_type(4)));
+  const long long n4 = n3 / 4, step = (long long)gridDim.x * blockDim.x;   // (fields are 256-byte aligned)
+  const long long t0 = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  for (long long e = t0; e < n4; e += step) {
+    const T4 a = ((const T4*)r0)[e], b = ((const T4*)r1)[e], c = ((const T4*)r2)[e], d = ((const T4*)r3)[e];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) add(a[k], b[k], c[k], d[k]);
+  }
+  if (t0 < n3 - 4 * n4) {
+    const long long e = 4 * n4 + t0;
+    add(r0[e], r1[e], r2[e], r3[e]);
   }
   block_sum<9>(acc, sh);
-  if (threadIdx.x == 0)
-#pragma unroll
-    for (int q = 0; q < 9; ++q) gpart[q * kPartRows + blockIdx.x] = acc[q];
+  if (threadIdx.x == 0) {
+    // column of the pair of slots (s, t), s <= t, is s (5 - s) / 2 + t; of slot s with R_i 6 + s
+    int k = 0;
+    for (int a = 0; a < 3; ++a) {
+      const int sa = (il - a + 1) % 3;
+      for (int b = a; b < 3; ++b, ++k) {
+        const int sb = (il - b + 1) % 3, lo = sa < sb ? sa : sb, hi = sa < sb ? sb : sa;
+        gpart[(lo * (5 - lo) / 2 + hi) * kPartRows + blockIdx.x] = acc[k];
+      }
+      gpart[(6 + sa) * kPartRows + blockIdx.x] = acc[6 + a];
+    }
+  }
 }
 
 __global__ __launch_bounds__(kBlock) void k_alpha3(DevState* st, const double* __restrict__ gpart, int nblk) {
-  __shared__ double sh[9 * 16];
+  __shared__ double acc[9];
   if (st->done || !st->accel) return;
-  double acc[9];
-#pragma unroll
-  for (int q = 0; q < 9; ++q) acc[q] = 0.0;
-  sum_cols<9>(gpart, kPartRows, nblk, acc);
-  block_sum<9>(acc, sh);
+  col_sums(gpart, kPartRows, nblk, 9, acc);
   if (threadIdx.x != 0) return;
   double G[3][4] = {{acc[0], acc[1], acc[2], acc[6]}, {acc[1], acc[3], acc[4], acc[7]}, {acc[2], acc[4], acc[5], acc[8]}};
   const double tr = G[0][0] + G[1][1] + G[2][2];
@@ -924,8 +840,6 @@ __global__ __launch_bounds__(kBlock) void k_reactions_d(Geo g, DeltaBufs<T> D, S
 // ---------------------------------------------------------------------------
 // launch wrappers
 // ---------------------------------------------------------------------------
-TileGrid residual_tiles(const Geo& g, bool inc);
-TileGrid residual_tiles_fp64(const Geo& g, bool gen);
 
 template <typename T, typename TS>
 int launch_delta_residual_ts(const Geo& g, const DeltaBufs<T>& D, const ContactDev& ct, DevState* st, double* part,
@@ -956,8 +870,8 @@ int launch_delta_residual(const Geo& g, const DeltaBufs<T>& D, const ContactDev&
   // each pass on the grid for its own resident count (the incremental one's taken only when
   // its segments are long enough); the control sums the largest count of rows, and a pass on
   // a smaller grid clears the rows beyond it
-  TileGrid tf = residual_tiles(g, false);
-  TileGrid ti = use_inc ? residual_tiles(g, true) : tf;
+  TileGrid tf = residual_tiles(g, gen, false);
+  TileGrid ti = use_inc ? residual_tiles(g, false, true) : tf;
   TileGrid tu = refine ? residual_tiles_fp64(g, gen) : tf;
   if (tf.tx > 0) {
     const int rows = std::max(tf.rows, std::max(ti.rows, tu.rows));
@@ -996,7 +910,9 @@ template <typename T>
 void launch_delta_control(const Geo& g, const DeltaBufs<T>& D, const ContactDev& ct, const WeakDev& w, DevState* st,
                           const double* part, const double* wpart, int nblk, hipStream_t s) {
   if (w.m > 0) hipLaunchKernelGGL(k_weak_d<T>, dim3(rel_grid(w.m)), dim3(kBlock), 0, s, g, D, w, st);
-  launch_control(st, part, nblk, wpart, w.m, ct, kPartStrideD, s);
+  // the tiled passes without contact or singular modes leave the two norms only
+  const bool gen = ct.on || g.sing[0] || g.sing[1] || g.sing[2] || residual_tiles(g, false, false).tx <= 0;
+  launch_control(st, part, nblk, wpart, w.m, ct, gen ? kPartStrideD : 2, s);
 }
 
 // Blocks of the tiled residual pass resident on the current device at once (blocks per CU
@@ -1051,27 +967,19 @@ static TileGrid tile_grid(const Geo& g, int tx, int ty, int seg) {
 // segments, at most kPartRows blocks (the partial-sum rows); tx = 0 when the node plane alone
 // needs more tiles than that.  A block marches its segment's planes plus two planes of
 // prologue, and the blocks run in rounds of the resident count, so the split taken is the
-// one with the fewest (rounds x planes per block); ties go to fewer segments.  inc: the split
-// for the resident count of the incremental pass is taken when its segments are at least 8
-// planes long (shorter ones add more prologue reads than the extra blocks save: measured at
-// 64^3, 2-plane segments on 990 blocks against 3-plane ones on 660; at 128^3 the 13-plane
-// segments on 950 blocks beat 17-plane ones on 760, 0.099 -> 0.089 ms).
-TileGrid residual_tiles(const Geo& g, bool inc) {
+// one with the fewest (rounds x planes per block); ties go to fewer segments.  Every
+// instance has its own split, for its own resident count: on another's grid it may run in two rounds.
+TileGrid residual_tiles(const Geo& g, bool gen, bool inc) {
   const int tx = (g.N[0] + kTX - 1) / kTX, ty = (g.N[1] + kTY - 1) / kTY;
   if ((long long)tx * ty > kPartRows) return TileGrid{0, 0, 0, 0, 0};
-  // finite strain: the PK1 instances hold two blocks per CU (LDS), the small-strain ones three
-  int bseg = tile_split(g, tx, ty,
-                        g.fs ? residual_resident<true, false, float, false>() : residual_resident<false, false, float, false>());
-  if (inc) {
-    const int iseg = tile_split(g, tx, ty, residual_resident<false, false, float, true>());
-    if (iseg >= 8) bseg = iseg;
-  }
-  return tile_grid(g, tx, ty, bseg);
+  int resident;
+  if (inc) resident = residual_resident<false, false, float, true>();
+  else if (g.fs) resident = gen ? residual_resident<true, true, float, false>() : residual_resident<true, false, float, false>();
+  else resident = gen ? residual_resident<false, true, float, false>() : residual_resident<false, false, float, false>();
+  return tile_grid(g, tx, ty, tile_split(g, tx, ty, resident));
 }
 
-// Tile grid of the pass with FP64 stresses, split for its own resident count (one or two
-// blocks per CU against three or four for the FP32 instances): on another pass's grid it ran
-// in two rounds.  gen: the instance for contact or singular modes.
+// Tile grid of the pass with FP64 stresses; gen: the instance for contact or singular modes.
 TileGrid residual_tiles_fp64(const Geo& g, bool gen) {
   const int tx = (g.N[0] + kTX - 1) / kTX, ty = (g.N[1] + kTY - 1) / kTY;
   if ((long long)tx * ty > kPartRows) return TileGrid{0, 0, 0, 0, 0};
@@ -1083,6 +991,8 @@ TileGrid residual_tiles_fp64(const Geo& g, bool gen) {
 
 template <typename T>
 void launch_delta_anderson(const DeltaBufs<T>& D, long long n3, DevState* st, double* gpart, int nblk, hipStream_t s) {
+  // four values per thread and step, two steps at least: on small grids the block sums set the time
+  nblk = (int)std::max<long long>(1, std::min<long long>(nblk, n3 / (8 * kBlock)));
   hipLaunchKernelGGL(k_gram3<T>, dim3(nblk), dim3(kBlock), 0, s, D, n3, st, gpart);
   hipLaunchKernelGGL(k_alpha3, dim3(1), dim3(kBlock), 0, s, st, gpart, nblk);
 }

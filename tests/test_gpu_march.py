@@ -1,0 +1,57 @@
+"""The marching residual pass of the FP32 form at the edges of its 31 x 7 node tiles: grids of a
+little less than a tile, exactly one and a little more, two-voxel axes, segments of one and of
+several planes, on every axis periodic, in small and finite strain, from u and incremental.  One
+step from random fields through the stage entry against the oracle; tolerances as in
+test_gpu_residual_form.py: 2e-5 with FP32 stresses, 2e-6 with FP64."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import tetra2
+from oracle.solver import Solver as OSolver
+from test_gpu_residual_form import _lib
+
+pytestmark = pytest.mark.gpu
+
+CASES = [((28, 5, 2), None), ((30, 6, 3), None), ((32, 7, 2), None), ((2, 2, 2), None), ((2, 14, 40), None),
+         ((60, 2, 9), None), ((32, 7, 5), 0), ((30, 7, 5), 0), ((30, 7, 5), 1), ((32, 8, 2), 2), ((63, 13, 33), None)]
+
+
+@pytest.mark.parametrize("idx", range(len(CASES)))
+@pytest.mark.parametrize("form", ["fp32", "fp64_stress", "incremental", "finite_strain"])
+def test_march_at_tile_edges(idx, form):
+    F = _lib()
+    n, per = CASES[idx]
+    fs, f64, inc = form == "finite_strain", form == "fp64_stress", form == "incremental"
+    print(f"[march] n={n} periodic={per} {form}", flush=True)
+    rng = np.random.default_rng(1300 + idx)
+    lam = rng.uniform(0.4, 2.5, n[::-1]); mu = rng.uniform(0.3, 1.8, n[::-1])
+    bc = rng.integers(0, 2, (3, 3, 2)).astype(np.int8)
+    bc[:, 0, 0] = W.BC_D          # no singular mode
+    if per is not None:
+        bc[:, per, :] = W.BC_P
+        bc[:, (per + 1) % 3, 0] = W.BC_D
+    o = OSolver(n, lam, mu, bc, r0_factor=1.3, finite_strain=fs)
+    g = F.Solver(n, lam, mu, bc, r0_factor=1.3, precision="fp32", finite_strain=fs)
+    A = o.plan.amask
+    free = ~A
+
+    def field(scale):
+        f = rng.standard_normal(o.zeros().shape) * scale
+        f[A] = 0.0
+        return f
+
+    u, delta, e, R_prev = field(2e-2), field(1e-3), field(2e-2), field(2e-2)
+    pe = o.iterate_parts(u)["p"]
+    p_prev = o.iterate_parts(u - delta)["p"] if inc else field(2e-2)
+    k0d = -o.reference_term(tetra2.tet_gradients(delta, o.plan))
+    p, R, dR, dY, sums = g.stage_residual_form(u, delta, e, p_prev, R_prev, 3, incremental=inc,
+                                               fp64_stress=int(f64))
+    tol = 2e-6 if f64 else 2e-5
+    Re = pe + k0d - e
+    dYe = pe - p_prev + k0d
+    assert np.abs(p - pe).max() <= tol * np.abs(pe).max()
+    assert abs(sums[0] - np.sum(pe[free] ** 2)) <= 10 * tol * np.sum(pe[free] ** 2)
+    assert np.abs(R - Re)[free].max() <= tol * np.abs(Re).max()
+    assert np.abs(dR - (Re - R_prev))[free].max() <= tol * np.abs(Re - R_prev).max()
+    assert np.abs(dY - dYe)[free].max() <= tol * np.abs(dYe).max()
