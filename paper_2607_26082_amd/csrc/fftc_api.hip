@@ -613,10 +613,10 @@ void enqueue_iteration(fftc_problem* h, StageTimer* tm = nullptr, int which = L_
       launch_flags_combine<T>(B, n3, h->st, 1, s);
     }
     if (tm) tm->mark(s);
-    launch_residual<T>(h->g, B, ct, h->st, h->part, h->nblk_res, 0, 0, s);
+    const int nres = launch_residual<T>(h->g, B, ct, h->st, h->part, h->nblk_res, 0, 0, s);
     if (tm) tm->mark(s);
     launch_weak<T>(h->g, B, w, h->st, 0, s);
-    launch_control(h->st, h->part, h->nblk_res, h->wpart, w.m, ct, kPartStride, s);
+    launch_control(h->st, h->part, nres, h->wpart, w.m, ct, kPartStride, s);
     if (tm) tm->mark(s);
   }
   if (!(parts & TAIL)) return;
@@ -915,29 +915,30 @@ int stage_residual_t(fftc_problem* h, const double* u_dev, double* p_dev, double
   const WeakDev w = weak_dev(h);
   DevState hs{};
   HIPCHK(h, hipMemcpyAsync(h->st, &hs, sizeof(DevState), hipMemcpyHostToDevice, s));
+  int nres = 0;
   for (int pass = 0; pass < 2; ++pass) {
     double* dst = pass == 0 ? ptil_dev : p_dev;
     if (!dst) continue;
-    launch_residual<T>(h->g, B, ct, h->st, h->part, h->nblk_res, 1, pass, s);
+    nres = launch_residual<T>(h->g, B, ct, h->st, h->part, h->nblk_res, 1, pass, s);
     launch_weak<T>(h->g, B, w, h->st, 1, s);
     launch_convert<T, double>(B.X, dst, n3, s);
   }
   if (sums) {
     if (!ptil_dev && !p_dev) {
-      launch_residual<T>(h->g, B, ct, h->st, h->part, h->nblk_res, 1, 0, s);
+      nres = launch_residual<T>(h->g, B, ct, h->st, h->part, h->nblk_res, 1, 0, s);
       launch_weak<T>(h->g, B, w, h->st, 1, s);
     }
     // the first two columns of the partial-sum table: ||p||^2 and ||sigma||^2 per block
-    std::vector<double> part(2 * (size_t)h->nblk_res), wp(w.m + 1);
+    std::vector<double> part(2 * (size_t)nres), wp(w.m + 1);
     for (int q = 0; q < 2; ++q)
-      HIPCHK(h, hipMemcpyAsync(part.data() + (size_t)q * h->nblk_res, h->part + (size_t)q * kPartRows,
-                               8 * (size_t)h->nblk_res, hipMemcpyDeviceToHost, s));
+      HIPCHK(h, hipMemcpyAsync(part.data() + (size_t)q * nres, h->part + (size_t)q * kPartRows,
+                               8 * (size_t)nres, hipMemcpyDeviceToHost, s));
     if (w.m) HIPCHK(h, hipMemcpyAsync(wp.data(), h->wpart, 8 * w.m, hipMemcpyDeviceToHost, s));
     HIPCHK(h, hipStreamSynchronize(s));
     double a0 = 0, a1 = 0;
-    for (int b = 0; b < h->nblk_res; ++b) {
+    for (int b = 0; b < nres; ++b) {
       a0 += part[b];
-      a1 += part[(size_t)h->nblk_res + b];
+      a1 += part[(size_t)nres + b];
     }
     for (long long r = 0; r < w.m; ++r) a0 += wp[r];
     sums[0] = a0;
@@ -1573,6 +1574,8 @@ int bind_impl(fftc_h h, void* ws, size_t bytes, void* stream, bool tune, bool ma
   (void)residual_tiles(h->g, false, true);
   (void)residual_tiles_fp64(h->g, false);
   (void)residual_tiles_fp64(h->g, true);
+  (void)residual_tiles_literal<double>(h->g);
+  (void)residual_tiles_literal<float>(h->g);
   if (h->nblk_res >= 8) h->nblk_res -= h->nblk_res % 8;   // whole slabs per XCD
   if (h->nblk_res < 1) h->nblk_res = 1;
   for (int q = 0; q < h->nlit; ++q)

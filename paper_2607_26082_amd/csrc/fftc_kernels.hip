@@ -12,6 +12,7 @@
 //   k_proj_*     proj_U: relations (eq 11, eq 15), contact radial projection, strong DOFs
 #include "fftc_internal.h"
 #include "fftc_launch.h"
+#include "fftc_march.h"
 #include "fftc_common.h"
 
 #include <math.h>
@@ -248,6 +249,47 @@ __device__ __forceinline__ void node_eval_any(const Geo& g, const T* __restrict_
 // ---------------------------------------------------------------------------
 // Residual pass
 // ---------------------------------------------------------------------------
+// proj_P of the strong conditions and the obstacle at one node of mask m, its part of |p|^2 into pn2,
+// and p (write_p) or p + K0 u into X
+template <typename T>
+__device__ __forceinline__ void residual_tail(const Geo& g, const Bufs<T>& B, const ContactDev& ct, int cur, int i, int j,
+                                              int k, long long node, uint8_t m, T p[3], const T k0[3], int write_p,
+                                              double& pn2) {
+  const long long Nn = g.Nn;
+  if (ct.on && (m & M_FACE)) {
+    const int xyz[3] = {i, j, k};
+    const long long f = (long long)xyz[ct.b1] + (long long)g.N[ct.b1] * xyz[ct.b2];
+    const double X0 = i + (double)B.u[node], X1 = j + (double)B.u[Nn + node], X2 = k + (double)B.u[2 * Nn + node];
+    const double d0 = X0 - ct.center[0], d1 = X1 - ct.center[1], d2 = X2 - ct.center[2];
+    const double rr = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
+    const double gap = rr - ct.radius;
+    const double n0 = -d0 / rr, n1 = -d1 / rr, n2 = -d2 / rr;
+    const double pn = (double)p[0] * n0 + (double)p[1] * n1 + (double)p[2] * n2;
+    const int b = bcount(g, xyz);
+    const double fnc = -pn / (double)(1 << b);
+    const uint8_t inC = ct.C[f];
+    if (inC) {
+      p[0] = (T)((double)p[0] - pn * n0);
+      p[1] = (T)((double)p[1] - pn * n1);
+      p[2] = (T)((double)p[2] - pn * n2);
+    }
+    ct.V[cur][f] = (uint8_t)(((!inC) && gap < 0.0) ? 1 : 0) | (uint8_t)((inC && fnc > 0.0) ? 2 : 0);
+    ct.fnc[f] = fnc;
+    ct.gap[f] = gap;
+    pn2 += (double)p[0] * p[0] + (double)p[1] * p[1] + (double)p[2] * p[2];
+  } else {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      if (m & (M_STRONG << c)) p[c] = T(0);
+      else if (!(m & (M_WEAK << c))) pn2 += (double)p[c] * p[c];
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) B.X[c * Nn + node] = write_p ? p[c] : p[c] + k0[c];
+}
+
+// One node per thread, its neighbours through the caches: HEX1, and node planes wider than
+// kPartRows tiles.
 template <typename T, bool FS, bool HEX>
 __global__ __launch_bounds__(kBlock) void k_residual(Geo g, Bufs<T> B, ContactDev ct, DevState* st,
                                                      double* __restrict__ part, int force, int write_p) {
@@ -273,37 +315,166 @@ __global__ __launch_bounds__(kBlock) void k_residual(Geo g, Bufs<T> B, ContactDe
     acc[1] += sn;
 #pragma unroll
     for (int q = 0; q < 6; ++q) acc[2 + q] += ms[q];
-    const uint8_t m = B.mask[node];
-    if (ct.on && (m & M_FACE)) {
-      const int xyz[3] = {i, j, k};
-      const long long f = (long long)xyz[ct.b1] + (long long)g.N[ct.b1] * xyz[ct.b2];
-      const double X0 = i + (double)B.u[node], X1 = j + (double)B.u[Nn + node], X2 = k + (double)B.u[2 * Nn + node];
-      const double d0 = X0 - ct.center[0], d1 = X1 - ct.center[1], d2 = X2 - ct.center[2];
-      const double rr = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
-      const double gap = rr - ct.radius;
-      const double n0 = -d0 / rr, n1 = -d1 / rr, n2 = -d2 / rr;
-      const double pn = (double)p[0] * n0 + (double)p[1] * n1 + (double)p[2] * n2;
-      const int b = bcount(g, xyz);
-      const double fnc = -pn / (double)(1 << b);
-      const uint8_t inC = ct.C[f];
-      if (inC) {
-        p[0] = (T)((double)p[0] - pn * n0);
-        p[1] = (T)((double)p[1] - pn * n1);
-        p[2] = (T)((double)p[2] - pn * n2);
+    residual_tail<T>(g, B, ct, cur, i, j, k, node, B.mask[node], p, k0, write_p, acc[0]);
+  }
+  block_sum<kPartStride>(acc, sh);
+  if (threadIdx.x == 0)
+#pragma unroll
+    for (int q = 0; q < kPartStride; ++q) part[q * kPartRows + blockIdx.x] = acc[q];
+}
+
+// The TETRA2 pass on tiles (fftc_march.h): u staged in a ring of three planes; K0 u carried as
+// Kz = A_z + S_{z-1} and S_z, where A = st0 u + st1 (in-plane diagonal neighbours) and S = st2 (x
+// neighbours) + st3 (y neighbours) of a plane, so that a plane is read from LDS once.
+// Bound by the latency of a step at two blocks per CU (182 VGPRs, 59 KB of LDS), then by FP64
+// issue: at 128^3 76 us for 137 MB (157 us with one node per thread, every node forming its 24
+// corner forces from 39 values of u out of the caches), at 64^3 26 us (49), at 16^3 14 us (20).
+template <typename T, bool FS>
+__global__ __launch_bounds__(256) void k_residual_t(Geo g, Bufs<T> B, ContactDev ct, DevState* st,
+                                                    double* __restrict__ part, int force, int write_p, TileGrid tg) {
+  __shared__ T su[3][3][kHY][kHX];
+  __shared__ T sx[2][9][kVY][kVX];
+  __shared__ double sh[kPartStride * 16];
+  if (!force && st->done) return;
+  double acc[kPartStride];
+#pragma unroll
+  for (int q = 0; q < kPartStride; ++q) acc[q] = 0.0;
+  const int tid = threadIdx.x;
+  const int b = xcd_tile(blockIdx.x, gridDim.x);
+  const int bx = b % tg.tx, by = (b / tg.tx) % tg.ty, bz = b / (tg.tx * tg.ty);
+  const int x0 = bx * kTX, y0 = by * kTY;
+  const int Nx = g.N[0], Ny = g.N[1], Nz = g.N[2], NxNy = Nx * Ny;
+  const int zb = bz * tg.seg, ze = min(zb + tg.seg, Nz);
+  const int cur = ct.on ? st->vpar : 0;
+  int off[kPR];
+  plane_offsets(g, x0, y0, tid, off);
+  T rd[kPR];
+  auto fetch = [&](int pz) {
+    const int mz = mirror_coord(g, pz, 2);
+    const bool okz = mz >= 0 && mz < Nz;
+#pragma unroll
+    for (int r = 0; r < kPR; ++r) {
+      rd[r] = T(0);
+      if (okz && off[r] >= 0) rd[r] = B.u[off[r] + NxNy * mz];
+    }
+  };
+  auto commit = [&](int pz) {
+#pragma unroll
+    for (int r = 0; r < kPR; ++r) {
+      const int e = tid + 256 * r;
+      if (e < kPlane) (&su[ring3(pz)][0][0][0])[e] = rd[r];
+    }
+  };
+  const int lx = tid & (kVX - 1), ly = tid / kVX;
+  const int i = x0 - 1 + lx, j = y0 - 1 + ly;   // the thread's node, and its voxel's corner 000
+  const bool nact = lx >= 1 && ly >= 1 && i < Nx && j < Ny;
+  const VoxelXY vox = voxel_xy(g, i, j);
+  const bool own = lx >= 1 && ly >= 1 && i < g.n[0] && j < g.n[1];   // voxel whose sums this block adds
+  const NodeXY nxy = node_xy(g, i, j);
+  const int wx = lx >= 1 ? lx - 1 : 0, sy = ly >= 1 ? ly - 1 : 0;   // (unused values of the halo threads)
+  auto read_corners = [&](int pz, T (&cn)[4][3]) {
+    const int r = ring3(pz);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      cn[0][c] = su[r][c][ly][lx];
+      cn[1][c] = su[r][c][ly][lx + 1];
+      cn[2][c] = su[r][c][ly + 1][lx];
+      cn[3][c] = su[r][c][ly + 1][lx + 1];
+    }
+  };
+  auto read_stencil = [&](int pz, const T (&cn)[4][3], T (&A)[3], T (&S)[3]) {
+    const int r = ring3(pz);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const T dw = su[r][c][ly][wx], ds = su[r][c][sy][lx];
+      const T dsw = su[r][c][sy][wx], dse = su[r][c][sy][lx + 1], dnw = su[r][c][ly + 1][wx];
+      A[c] = T(g.st[c][0]) * cn[0][c] + T(g.st[c][1]) * ((dsw + dse) + (dnw + cn[3][c]));
+      S[c] = T(g.st[c][2]) * (dw + cn[1][c]) + T(g.st[c][3]) * (ds + cn[2][c]);
+    }
+  };
+  T lam, mu;
+  T lo[4][3];   // corners of the lower plane of the current layer
+  T fu[4][3];   // forces of the layer below on its upper corners
+  T Kz[3], S0[3];
+  fetch(zb - 1);
+  commit(zb - 1);
+  fetch(zb);
+  commit(zb);
+  fetch(zb + 1);
+  voxel_lame(g, vox, zb - 1, B.lam, B.mu, lam, mu);
+  __syncthreads();
+  {
+    T up[4][3], fl[4][3], vs = T(0), ms[6], A[3], S[3];
+    read_corners(zb - 1, lo);
+    read_corners(zb, up);
+    read_stencil(zb - 1, lo, A, S);
+    read_stencil(zb, up, A, S0);
+    voxel_forces<T, T, FS, false>(lo, up, lam, mu, fl, fu, vs, ms);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) Kz[c] = A[c] + S[c];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) lo[k][c] = up[k][c];
+  }
+  voxel_lame(g, vox, zb, B.lam, B.mu, lam, mu);
+  commit(zb + 1);   // (a third slot: no thread reads it before the barrier)
+  if (zb + 1 < ze) fetch(zb + 2);
+  __syncthreads();
+  for (int z = zb; z < ze; ++z) {
+    const long long node = (long long)i + (long long)Nx * j + (long long)NxNy * z;
+    const uint8_t m = nact ? B.mask[node] : 0;
+    T (*ex)[kVY][kVX] = sx[z & 1];
+    T F0[3];   // forces on the thread's own corner (0, 0)
+    {
+      T up[4][3], fl[4][3], fn[4][3];
+      T vs = T(0), ms[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
+      read_corners(z + 1, up);
+      voxel_forces<T, T, FS, true>(lo, up, lam, mu, fl, fn, vs, ms);
+      if (own) {
+        acc[1] += 8.0 * (double)vs;   // (1/2) sigma : sigma
+#pragma unroll
+        for (int q = 0; q < 6; ++q) acc[2 + q] += 2.0 * (double)ms[q];
       }
-      ct.V[cur][f] = (uint8_t)(((!inC) && gap < 0.0) ? 1 : 0) | (uint8_t)((inC && fnc > 0.0) ? 2 : 0);
-      ct.fnc[f] = fnc;
-      ct.gap[f] = gap;
-      acc[0] += (double)p[0] * p[0] + (double)p[1] * p[1] + (double)p[2] * p[2];
-    } else {
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        if (m & (M_STRONG << c)) p[c] = T(0);
-        else if (!(m & (M_WEAK << c))) acc[0] += (double)p[c] * p[c];
+        F0[c] = fl[0][c] + fu[0][c];
+#pragma unroll
+        for (int k = 1; k < 4; ++k) ex[3 * (k - 1) + c][ly][lx] = fl[k][c] + fu[k][c];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          fu[k][c] = fn[k][c];
+          lo[k][c] = up[k][c];
+        }
       }
     }
+    if (z + 1 < ze) {
+      voxel_lame(g, vox, z + 1, B.lam, B.mu, lam, mu);
+      commit(z + 2);
+    }
+    if (z + 2 < ze) fetch(z + 3);
+    __syncthreads();
+    T A1[3], S1[3];
+    read_stencil(z + 1, lo, A1, S1);
+    if (nact) {
+      const NodeXY nz_ = node_z(g, z);
+      const T w2b = T(1 << (nxy.b + nz_.b));
+      const int anti = nxy.anti | nz_.anti;
+      T p[3], k0[3];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) B.X[c * Nn + node] = write_p ? p[c] : p[c] + k0[c];
+      for (int c = 0; c < 3; ++c) {
+        const T F = (F0[c] + ex[c][ly][lx - 1]) + (ex[3 + c][ly - 1][lx] + ex[6 + c][ly - 1][lx - 1]);
+        const bool a = (anti >> c) & 1;
+        p[c] = a ? T(0) : -w2b * F;
+        k0[c] = a ? T(0) : Kz[c] + S1[c];
+      }
+      residual_tail<T>(g, B, ct, cur, i, j, z, node, m, p, k0, write_p, acc[0]);
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      Kz[c] = A1[c] + S0[c];
+      S0[c] = S1[c];
+    }
   }
   block_sum<kPartStride>(acc, sh);
   if (threadIdx.x == 0)
@@ -1071,16 +1242,34 @@ __global__ void k_extend(DevState* st, int iters, double tol) {
 // ---------------------------------------------------------------------------
 // launch wrappers
 // ---------------------------------------------------------------------------
+template <typename T, bool FS>
+static TileGrid literal_tiles(const Geo& g) {
+  static std::atomic<int> cache[64] = {};
+  return tile_grid_for(g, resident_blocks((const void*)k_residual_t<T, FS>, cache));
+}
 template <typename T>
-void launch_residual(const Geo& g, const Bufs<T>& B, const ContactDev& ct, DevState* st, double* part, int nblk,
-                     int force, int write_p, hipStream_t s) {
-  if (g.hex) {
-    if (g.fs) hipLaunchKernelGGL((k_residual<T, true, true>), dim3(nblk), dim3(kBlock), 0, s, g, B, ct, st, part, force, write_p);
-    else hipLaunchKernelGGL((k_residual<T, false, true>), dim3(nblk), dim3(kBlock), 0, s, g, B, ct, st, part, force, write_p);
-  } else {
-    if (g.fs) hipLaunchKernelGGL((k_residual<T, true, false>), dim3(nblk), dim3(kBlock), 0, s, g, B, ct, st, part, force, write_p);
-    else hipLaunchKernelGGL((k_residual<T, false, false>), dim3(nblk), dim3(kBlock), 0, s, g, B, ct, st, part, force, write_p);
+TileGrid residual_tiles_literal(const Geo& g) {
+  if (g.hex) return TileGrid{0, 0, 0, 0, 0};
+  return g.fs ? literal_tiles<T, true>(g) : literal_tiles<T, false>(g);
+}
+
+// Returns the partial rows left for the control step.
+template <typename T>
+int launch_residual(const Geo& g, const Bufs<T>& B, const ContactDev& ct, DevState* st, double* part, int nblk,
+                    int force, int write_p, hipStream_t s) {
+  const TileGrid tg = residual_tiles_literal<T>(g);
+  if (tg.tx > 0) {
+    const dim3 grid(tg.rows);
+    if (g.fs) hipLaunchKernelGGL((k_residual_t<T, true>), grid, dim3(256), 0, s, g, B, ct, st, part, force, write_p, tg);
+    else hipLaunchKernelGGL((k_residual_t<T, false>), grid, dim3(256), 0, s, g, B, ct, st, part, force, write_p, tg);
+    return tg.rows;
   }
+  const dim3 grid(nblk);
+  if (g.hex && g.fs) hipLaunchKernelGGL((k_residual<T, true, true>), grid, dim3(kBlock), 0, s, g, B, ct, st, part, force, write_p);
+  else if (g.hex) hipLaunchKernelGGL((k_residual<T, false, true>), grid, dim3(kBlock), 0, s, g, B, ct, st, part, force, write_p);
+  else if (g.fs) hipLaunchKernelGGL((k_residual<T, true, false>), grid, dim3(kBlock), 0, s, g, B, ct, st, part, force, write_p);
+  else hipLaunchKernelGGL((k_residual<T, false, false>), grid, dim3(kBlock), 0, s, g, B, ct, st, part, force, write_p);
+  return nblk;
 }
 
 template <typename T>
@@ -1180,7 +1369,8 @@ void launch_scale(double* x, long long n, double f, hipStream_t s) {
 }
 
 #define FFTC_INST(T)                                                                                              \
-  template void launch_residual<T>(const Geo&, const Bufs<T>&, const ContactDev&, DevState*, double*, int, int,   \
+  template TileGrid residual_tiles_literal<T>(const Geo&);                                                        \
+  template int launch_residual<T>(const Geo&, const Bufs<T>&, const ContactDev&, DevState*, double*, int, int,    \
                                    int, hipStream_t);                                                                  \
   template void launch_weak<T>(const Geo&, const Bufs<T>&, const WeakDev&, DevState*, int, hipStream_t);         \
   template void launch_anderson<T>(const Bufs<T>&, long long, DevState*, double*, int, int, hipStream_t);        \

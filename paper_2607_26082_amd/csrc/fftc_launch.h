@@ -5,7 +5,9 @@
 namespace fftc {
 
 template <typename T>
-void launch_residual(const Geo& g, const Bufs<T>& B, const ContactDev& ct, DevState* st, double* part, int nblk,
+TileGrid residual_tiles_literal(const Geo& g);
+template <typename T>
+int launch_residual(const Geo& g, const Bufs<T>& B, const ContactDev& ct, DevState* st, double* part, int nblk,
                      int force, int write_p, hipStream_t s);
 template <typename T>
 void launch_weak(const Geo& g, const Bufs<T>& B, const WeakDev& w, DevState* st, int force, hipStream_t s);

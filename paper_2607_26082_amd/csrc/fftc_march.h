@@ -12,6 +12,8 @@
 // exchange are double buffers, each rewritten only after the barrier that follows its last read.
 #pragma once
 
+#include <atomic>
+
 #include "fftc_internal.h"
 #include "fftc_common.h"
 
@@ -22,6 +24,19 @@ constexpr int kVX = kTX + 1, kVY = kTY + 1;   // voxels x0-1 .. x0+kTX-1
 constexpr int kHX = kTX + 2, kHY = kTY + 2;   // node tile with halo: x0-1 .. x0+kTX
 constexpr int kPlane = 3 * kHY * kHX;         // values of one staged node plane
 constexpr int kPR = (kPlane + 255) / 256;     // of them per thread
+
+int resident_blocks(const void* kernel, std::atomic<int> (&cache)[64]);
+TileGrid tile_grid_for(const Geo& g, int resident);
+
+// Tile of a block: contiguous ranges of tiles per XCD (blocks go to the 8 XCDs round-robin), so that
+// neighbouring tiles share their halo lines in one L2
+__device__ __forceinline__ int xcd_tile(unsigned p, unsigned G) {
+  const unsigned q = G / 8, r = G % 8, xcd = p % 8, slot = p / 8;
+  return (int)(xcd * q + (xcd < r ? xcd : r) + slot);
+}
+
+// slot of node plane pz (>= -1) in a ring of three
+__device__ __forceinline__ int ring3(int pz) { return (pz + 3) % 3; }
 
 // Offsets of the plane values thread tid stages, within a node plane (component and (x, y), the
 // stencil's mirror or periodic image outside the grid); -1: none
@@ -104,6 +119,37 @@ __device__ __forceinline__ void voxel_forces(const TU (&lo)[4][3], const TU (&up
         fu[3][r] = al + z;
       }
     }
+  }
+}
+
+// The voxel whose corner 000 is node (i, j), within a layer
+struct VoxelXY {
+  int at;
+  bool ok;   // inside the grid
+};
+__device__ __forceinline__ VoxelXY voxel_xy(const Geo& g, int i, int j) {
+  const int nx = g.n[0], ny = g.n[1];
+  bool ok = true;
+  if (g.periodic[0]) i = (i + nx) % nx;
+  else ok = i >= 0 && i < nx;
+  if (g.periodic[1]) j = (j + ny) % ny;
+  else ok = ok && j >= 0 && j < ny;
+  return VoxelXY{i + nx * j, ok};
+}
+// its Lame values in layer lz; 0 outside the grid
+template <typename T>
+__device__ __forceinline__ void voxel_lame(const Geo& g, const VoxelXY& v, int lz, const T* __restrict__ lam,
+                                           const T* __restrict__ mu, T& l, T& m) {
+  bool ok = v.ok;
+  const int nz = g.n[2];
+  int vz = lz;
+  if (g.periodic[2]) vz = (lz + nz) % nz;
+  else ok = ok && lz >= 0 && lz < nz;
+  l = m = T(0);
+  if (ok) {
+    const int at = v.at + g.n[0] * g.n[1] * vz;
+    l = lam[at];
+    m = mu[at];
   }
 }
 

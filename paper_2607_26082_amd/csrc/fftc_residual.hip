@@ -301,9 +301,6 @@ __global__ __launch_bounds__(kBlock) void k_residual_d(Geo g, DeltaBufs<T> D, Co
     for (int q = 0; q < kPartStrideD; ++q) part[q * kPartRows + blockIdx.x] = acc[q];
 }
 
-// slot of node plane pz (>= -1) in a ring of three
-__device__ __forceinline__ int ring3(int pz) { return (pz + 3) % 3; }
-
 // The tiled residual pass (see fftc_march.h).  Fields: u (FP64, passes from u) gives the stresses,
 // delta the reference-medium term K0 delta and, in the incremental pass (INC: small strain, no
 // contact or singular modes), the stresses: p_i = p_{i-1} + their divergence term; u is then not
@@ -332,14 +329,7 @@ void k_residual_dt(Geo g, DeltaBufs<T> D, ContactDev ct, DevState* st, double* _
   __shared__ double sh[NS * 16];
   if (st->done || res_pass(st) != (INC ? PASS_INC : (sizeof(TS) == 8 ? PASS_U64 : PASS_U))) return;
   const int tid = threadIdx.x;
-  // contiguous ranges of tiles per XCD (blocks go to the 8 XCDs round-robin), so that
-  // neighbouring tiles share their halo lines in one L2
-  int b;
-  {
-    const unsigned G = gridDim.x, p = blockIdx.x;
-    const unsigned q = G / 8, r = G % 8, xcd = p % 8, slot = p / 8;
-    b = (int)(xcd * q + (xcd < r ? xcd : r) + slot);
-  }
+  const int b = xcd_tile(blockIdx.x, gridDim.x);
   const int bx = b % tg.tx, by = (b / tg.tx) % tg.ty, bz = b / (tg.tx * tg.ty);
   const int x0 = bx * kTX, y0 = by * kTY;
   const int Nx = g.N[0], Ny = g.N[1], Nz = g.N[2];
@@ -388,26 +378,8 @@ void k_residual_dt(Geo g, DeltaBufs<T> D, ContactDev ct, DevState* st, double* _
   const int lx = tid & (kVX - 1), ly = tid / kVX;
   const int i = x0 - 1 + lx, j = y0 - 1 + ly;   // the thread's node, and its voxel's corner 000
   const bool nact = lx >= 1 && ly >= 1 && i < Nx && j < Ny;
-  int vx = i, vy = j;
-  bool vok = true;
-  if (g.periodic[0]) vx = (vx + nx) % nx;
-  else vok = vx >= 0 && vx < nx;
-  if (g.periodic[1]) vy = (vy + ny) % ny;
-  else vok = vok && vy >= 0 && vy < ny;
-  const int vxy = vx + nx * vy, nxny = nx * ny;
+  const VoxelXY vox = voxel_xy(g, i, j);
   const bool own = !INC && lx >= 1 && ly >= 1 && i < nx && j < ny;   // voxel whose norm this block counts
-  // Lame values of the thread's voxel in layer lz; 0 outside the grid
-  auto fetch_lm = [&](int lz, T& l, T& m) {
-    bool ok = vok;
-    int vz = lz;
-    if (g.periodic[2]) vz = (lz + nz) % nz;
-    else ok = ok && lz >= 0 && lz < nz;
-    l = m = T(0);
-    if (ok) {
-      l = D.lam[vxy + nxny * vz];
-      m = D.mu[vxy + nxny * vz];
-    }
-  };
   const NodeXY nxy = node_xy(g, i, j);
   const int wx = lx >= 1 ? lx - 1 : 0, sy = ly >= 1 ? ly - 1 : 0;   // (unused values of the halo threads)
   // corners of the thread's voxel in plane pz
@@ -457,7 +429,7 @@ void k_residual_dt(Geo g, DeltaBufs<T> D, ContactDev ct, DevState* st, double* _
   fetch(zb);
   commit(zb);
   fetch(zb + 1);
-  fetch_lm(zb - 1, lam, mu);
+  voxel_lame(g, vox, zb - 1, D.lam, D.mu, lam, mu);
   if (nact) tail_at(zb, tin);
   __syncthreads();
   {
@@ -476,7 +448,7 @@ void k_residual_dt(Geo g, DeltaBufs<T> D, ContactDev ct, DevState* st, double* _
 #pragma unroll
       for (int c = 0; c < 3; ++c) lo[k][c] = up[k][c];
   }
-  fetch_lm(zb, lam, mu);
+  voxel_lame(g, vox, zb, D.lam, D.mu, lam, mu);
   __syncthreads();
   commit(zb + 1);
   if (zb + 1 < ze) fetch(zb + 2);
@@ -505,7 +477,7 @@ void k_residual_dt(Geo g, DeltaBufs<T> D, ContactDev ct, DevState* st, double* _
     }
     // the next layer's and the next node's inputs are requested as soon as their registers are free
     if (z + 1 < ze) {
-      fetch_lm(z + 1, lam, mu);
+      voxel_lame(g, vox, z + 1, D.lam, D.mu, lam, mu);
       commit(z + 2);
     }
     if (z + 2 < ze) fetch(z + 3);
@@ -915,26 +887,25 @@ void launch_delta_control(const Geo& g, const DeltaBufs<T>& D, const ContactDev&
   launch_control(st, part, nblk, wpart, w.m, ct, gen ? kPartStrideD : 2, s);
 }
 
-// Blocks of the tiled residual pass resident on the current device at once (blocks per CU
-// at the kernel's register and LDS use, times the CU count), queried once per device and
-// instance: the pass with T stresses, the incremental one, or one with FP64 stresses.
-template <bool FS, bool GEN, typename TS, bool INC>
-static int residual_resident() {
-  static std::atomic<int> cache[64] = {};
+// Blocks of a residual pass instance resident on the current device at once (blocks per CU at
+// its register and LDS use, times the CU count), queried once per device and instance.
+int resident_blocks(const void* kernel, std::atomic<int> (&cache)[64]) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 512;
   int r = cache[dev].load(std::memory_order_relaxed);
   if (!r) {
     int per_cu = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_residual_dt<float, FS, GEN, TS, INC>, 256, 0) !=
-            hipSuccess ||
-        per_cu < 1)
-      per_cu = 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, 0) != hipSuccess || per_cu < 1) per_cu = 1;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 1;
     r = per_cu * cus;
     cache[dev].store(r, std::memory_order_relaxed);   // every thread computes the same value
   }
   return r;
+}
+template <bool FS, bool GEN, typename TS, bool INC>
+static int residual_resident() {
+  static std::atomic<int> cache[64] = {};
+  return resident_blocks((const void*)k_residual_dt<float, FS, GEN, TS, INC>, cache);
 }
 
 // segment length with the fewest (rounds x planes per block) for a resident count; ties go to
@@ -956,37 +927,33 @@ static int tile_split(const Geo& g, int tx, int ty, long long resident) {
   return bseg;
 }
 
-static TileGrid tile_grid(const Geo& g, int tx, int ty, int seg) {
-  TileGrid t{tx, ty, 0, seg, 0};
-  t.nseg = (g.N[2] + seg - 1) / seg;
+// Tile grid of a residual pass instance with this many resident blocks: tiles of kTX x kTY node
+// columns, z split into segments, at most kPartRows blocks (the partial-sum rows); tx = 0 when the
+// node plane alone needs more tiles than that.  A block marches its segment's planes plus two
+// planes of prologue, and the blocks run in rounds of the resident count, so the split taken is
+// the one with the fewest (rounds x planes per block); ties go to fewer segments.  Every instance
+// has its own split: on another's grid it may run in two rounds.
+TileGrid tile_grid_for(const Geo& g, int resident) {
+  const int tx = (g.N[0] + kTX - 1) / kTX, ty = (g.N[1] + kTY - 1) / kTY;
+  if ((long long)tx * ty > kPartRows) return TileGrid{0, 0, 0, 0, 0};
+  TileGrid t{tx, ty, 0, tile_split(g, tx, ty, resident), 0};
+  t.nseg = (g.N[2] + t.seg - 1) / t.seg;
   t.rows = tx * ty * t.nseg;
   return t;
 }
 
-// Tile grid of the tiled residual pass: tiles of kTX x kTY node columns, z split into
-// segments, at most kPartRows blocks (the partial-sum rows); tx = 0 when the node plane alone
-// needs more tiles than that.  A block marches its segment's planes plus two planes of
-// prologue, and the blocks run in rounds of the resident count, so the split taken is the
-// one with the fewest (rounds x planes per block); ties go to fewer segments.  Every
-// instance has its own split, for its own resident count: on another's grid it may run in two rounds.
+// gen: the instance for contact or singular modes; inc: the incremental pass
 TileGrid residual_tiles(const Geo& g, bool gen, bool inc) {
-  const int tx = (g.N[0] + kTX - 1) / kTX, ty = (g.N[1] + kTY - 1) / kTY;
-  if ((long long)tx * ty > kPartRows) return TileGrid{0, 0, 0, 0, 0};
-  int resident;
-  if (inc) resident = residual_resident<false, false, float, true>();
-  else if (g.fs) resident = gen ? residual_resident<true, true, float, false>() : residual_resident<true, false, float, false>();
-  else resident = gen ? residual_resident<false, true, float, false>() : residual_resident<false, false, float, false>();
-  return tile_grid(g, tx, ty, tile_split(g, tx, ty, resident));
+  if (inc) return tile_grid_for(g, residual_resident<false, false, float, true>());
+  if (g.fs)
+    return tile_grid_for(g, gen ? residual_resident<true, true, float, false>() : residual_resident<true, false, float, false>());
+  return tile_grid_for(g, gen ? residual_resident<false, true, float, false>() : residual_resident<false, false, float, false>());
 }
-
-// Tile grid of the pass with FP64 stresses; gen: the instance for contact or singular modes.
+// the pass with FP64 stresses
 TileGrid residual_tiles_fp64(const Geo& g, bool gen) {
-  const int tx = (g.N[0] + kTX - 1) / kTX, ty = (g.N[1] + kTY - 1) / kTY;
-  if ((long long)tx * ty > kPartRows) return TileGrid{0, 0, 0, 0, 0};
-  int resident;
-  if (g.fs) resident = gen ? residual_resident<true, true, double, false>() : residual_resident<true, false, double, false>();
-  else resident = gen ? residual_resident<false, true, double, false>() : residual_resident<false, false, double, false>();
-  return tile_grid(g, tx, ty, tile_split(g, tx, ty, resident));
+  if (g.fs)
+    return tile_grid_for(g, gen ? residual_resident<true, true, double, false>() : residual_resident<true, false, double, false>());
+  return tile_grid_for(g, gen ? residual_resident<false, true, double, false>() : residual_resident<false, false, double, false>());
 }
 
 template <typename T>
