@@ -269,14 +269,16 @@ struct Layout {
 };
 
 // Axes whose transforms run as matrix products (fftc_dense.hip): up to 256 nodes, every length
-// without a compile-time FFT and every periodic axis (per iteration, products against the
-// runtime-length FFT: 30x22x26 FP64 88 against 165 us, 75x140x18 FP32 139 against 256, 140^3 FP32
-// 692 against 1672 and FP64 832 against 1244, 256x256x16 periodic FP32 372 against 412); of the
-// compile-time lengths 16, 32 and 48 on grids of at most 160,000 nodes, where the passes are bound by
-// their chain of barriers (32^3 94 against 107 us in FP64; at 64^3 167 against 162).
+// without a compile-time FFT (per iteration, products against the runtime-length FFT: 30x22x26
+// FP64 88 against 165 us, 75x140x18 FP32 139 against 256, 140^3 FP32 692 against 1672 and FP64 832
+// against 1244).  Of the compile-time lengths 16, 32 and 48 on grids of at most 160,000 nodes, where
+// the passes are bound by their chain of barriers, in FP32 (at 64^3 167 against 162) and on
+// periodic axes (a y pass at 48^3 periodic 8.4 against 9.2 us in FP64; longer periodic lines the
+// other way: 64^3 12 against 10, 256x256x16 57 against 25, in FP32 57 against 17).
 bool dense_axis(const fftc_problem* h, int J) {
   if (h->N[J] > 256) return false;
-  return h->periodic[J] || !dtt_compiled(h->n[J]) || (h->precision == FFTC_FP32 && h->n[J] <= 48 && h->Nn <= 160000);
+  return !dtt_compiled(h->n[J]) ||
+         (h->n[J] <= 48 && h->Nn <= 160000 && (h->precision == FFTC_FP32 || h->periodic[J]));
 }
 
 // carve the workspace; with base == nullptr only computes the size.  mats: with the transform
@@ -1546,7 +1548,7 @@ int bind_impl(fftc_h h, void* ws, size_t bytes, void* stream, bool tune, bool ma
     const int cand[2] = {h->precision == FFTC_FP64 ? 128 : 256, h->precision == FFTC_FP64 ? 256 : 512};
     for (int p = 0; p < TP_N; ++p) {
       h->dtt_nt[p] = cand[1];
-      if (h->periodic[axis[p]] || !dtt_compiled(h->n[axis[p]])) continue;   // one block size
+      if (!dtt_compiled(h->n[axis[p]]) || h->mat[axis[p]][h->type[0][axis[p]]]) continue;   // one block size
       for (int v = 0; v < 2; ++v) {
         h->dtt_nt[p] = cand[v];
         float tot = 0.f;

@@ -8,6 +8,7 @@
 //   DCT2 / DCT3: reordering of the samples (even indices ascending, odd descending) and a
 //                quarter-wave twiddle e^{-/+ i pi k / 2n}
 //   DST2 / DST3: DCT2 / DCT3 with alternating signs and reversed indices.
+// A periodic line is transformed as n complex points with zero imaginary parts.
 // The FFT runs in registers, two radix passes (8, 12 or 16 points per thread) joined by
 // one LDS exchange, Stockham order.  One block transforms LB lines of one component.
 #pragma once
@@ -218,6 +219,21 @@ __device__ __forceinline__ T post_ct(int type, int inv, const cplx<T>* Zb, int m
   if (m == 0) return T(0);
   const int kk = n - m;
   return cmul(tw[kk], Z(kk)).re * T(1.0 / n);
+}
+
+// Half-complex DFT of a periodic line (storage: real parts of bins 0 .. n / 2, then imaginary parts of
+// bins n / 2 - 1 .. 1) and its inverse
+template <typename T, int NF>
+__device__ __forceinline__ cplx<T> pre_dft(int inv, const T* x, int k) {
+  const T v = x[k <= NF / 2 ? k : NF - k];
+  if (!inv) return {x[k], T(0)};
+  if (k == 0 || 2 * k == NF) return {v, T(0)};
+  return 2 * k < NF ? cplx<T>{v, x[NF - k]} : cplx<T>{v, -x[k]};
+}
+template <typename T, int NF>
+__device__ __forceinline__ T post_dft(int inv, const cplx<T>* Zb, int m) {
+  if (inv) return Zb[cpad<NF>(m)].re * T(1.0 / NF);
+  return 2 * m <= NF ? Zb[cpad<NF>(m)].re : Zb[cpad<NF>(NF - m)].im;
 }
 
 // Complex FFT of LB lines of length NF held in LDS (cb, line stride CS); the first pass

@@ -426,7 +426,7 @@ __global__ __launch_bounds__(kBlock) void k_dtt(DttArgs<T> a) {
 }
 
 // ---------------------------------------------------------------------------
-// DTT pass with a compile-time length (non-periodic axes, n in {16,32,48,64,96,128,256})
+// DTT pass with a compile-time length (n in {16,32,48,64,96,128,256}); TY = T_DFT: periodic axis
 // ---------------------------------------------------------------------------
 template <typename T, int NF, int NTH, int TY = -1>
 __global__ __launch_bounds__(NTH) void k_dtt2(DttArgs<T> a) {
@@ -483,6 +483,16 @@ __global__ __launch_bounds__(NTH) void k_dtt2(DttArgs<T> a) {
   const cplx<T>* tw = tws;
   // TY >= 0: every component of this pass has transform type TY (fixed at compile time)
   const int type = TY >= 0 ? TY : a.types[c];
+  // a periodic line (TY = T_DFT) has no node NF
+  constexpr bool PER = TY == T_DFT;
+  auto pre = [&](int inv, const T* x, int k) {
+    if constexpr (PER) return pre_dft<T, NF>(inv, x, k);
+    else return pre_ct<T, NF>(type, inv, x, k, tw);
+  };
+  auto post = [&](int inv, const cplx<T>* Z, int m) {
+    if constexpr (PER) return post_dft<T, NF>(inv, Z, m);
+    else return post_ct<T, NF>(type, inv, Z, m, tw);
+  };
   const unsigned tid = threadIdx.x;
   constexpr int TL = NF / FftPlan<NF>::R1;   // threads per line in the FFT passes
   constexpr int NB = FftPlan<NF>::R1;        // body nodes (m < NF) per thread: LB NF = NT NB
@@ -512,7 +522,7 @@ __global__ __launch_bounds__(NTH) void k_dtt2(DttArgs<T> a) {
     else f(std::integral_constant<int, 0>{});
   };
   const unsigned ls = (unsigned)lstride, es = (unsigned)estride;
-  const bool has_tail = tid < (unsigned)LB;
+  const bool has_tail = !PER && tid < (unsigned)LB;
   const bool tail_ok = has_tail && (int)tid < nl;
   const unsigned tail_off = tid * ls + (unsigned)NF * es;
   // gather the real lines into LDS: all loads of a thread are issued before any store (the
@@ -620,7 +630,7 @@ __global__ __launch_bounds__(NTH) void k_dtt2(DttArgs<T> a) {
   __syncthreads();
   const int inv_first = (a.mode == PASS_INV);
   {
-    auto ld = [&](int l, int k) { return pre_ct<T, NF>(type, inv_first, rb + l * RS, k, tw); };
+    auto ld = [&](int l, int k) { return pre(inv_first, rb + l * RS, k); };
     if (fft_sign(type, inv_first) < 0) fft_ct<T, NF, -1, NT>(cb, CS, tw, ld);
     else fft_ct<T, NF, +1, NT>(cb, CS, tw, ld);
   }
@@ -644,7 +654,7 @@ __global__ __launch_bounds__(NTH) void k_dtt2(DttArgs<T> a) {
     const T thr = (T)a.thr[c];
     const unsigned x0 = bxi * LB;
     auto green = [&](unsigned l, unsigned m) -> T {
-      const T v = post_ct<T, NF>(type, 0, cb + l * CS, m, tw);
+      const T v = post(0, cb + l * CS, m);
       const T sx = (T)sxT[x0 + l], qx = (T)qxT[x0 + l];
       const T A = T(4) * (a0 * sx * qy + a1 * sy * qx + e2 * sx * sy);
       const T B = T(4) * (e0 * qx * sy + e1 * qy * sx + a2 * qx * qy);
@@ -673,7 +683,7 @@ __global__ __launch_bounds__(NTH) void k_dtt2(DttArgs<T> a) {
     }
     if (has_tail) rb[tid * RS + NF] = vals[NB];
     __syncthreads();
-    auto ld = [&](int l, int k) { return pre_ct<T, NF>(type, 1, rb + l * RS, k, tw); };
+    auto ld = [&](int l, int k) { return pre(1, rb + l * RS, k); };
     if (fft_sign(type, 1) < 0) fft_ct<T, NF, -1, NT>(cb, CS, tw, ld);
     else fft_ct<T, NF, +1, NT>(cb, CS, tw, ld);
   }
@@ -715,10 +725,10 @@ __global__ __launch_bounds__(NTH) void k_dtt2(DttArgs<T> a) {
       for (int i = 0; i < NB; ++i) {
         unsigned l, m;
         body(mk, i, l, m);
-        const T v = post_ct<T, NF>(type, inv_out, cb + l * CS, m, tw);
+        const T v = post(inv_out, cb + l * CS, m);
         if (!G || (int)l < nl) upd(v, l, m, l * ls + m * es, uo[i]);
       }
-      if (tail_ok) upd(post_ct<T, NF>(type, inv_out, cb + tid * CS, NF, tw), tid, NF, tail_off, uo[NB]);
+      if (tail_ok) upd(post(inv_out, cb + tid * CS, NF), tid, NF, tail_off, uo[NB]);
     };
     if (axis != 0) update(std::integral_constant<int, 1>{}, std::true_type{});
     else if (nl >= LB) update(std::integral_constant<int, 0>{}, std::false_type{});
@@ -733,14 +743,14 @@ __global__ __launch_bounds__(NTH) void k_dtt2(DttArgs<T> a) {
     for (int i = 0; i < NB; ++i) {
       unsigned l, m;
       body(mk, i, l, m);
-      const T v = post_ct<T, NF>(type, inv_out, cb + l * CS, m, tw);
+      const T v = post(inv_out, cb + l * CS, m);
       if (!decltype(guarded)::value || (int)l < nl) out[l * ls + m * es] = v;
     }
   };
   if (axis != 0) store(std::integral_constant<int, 1>{}, std::true_type{});
   else if (nl >= LB) store(std::integral_constant<int, 0>{}, std::false_type{});
   else store(std::integral_constant<int, 0>{}, std::true_type{});
-  if (tail_ok) out[tail_off] = post_ct<T, NF>(type, inv_out, cb + tid * CS, NF, tw);
+  if (tail_ok) out[tail_off] = post(inv_out, cb + tid * CS, NF);
 }
 
 template <typename T>
@@ -764,6 +774,10 @@ static void launch_dtt2(const DttArgs<T>& a, hipStream_t s) {
 // that type fixed at compile time (no per-element type dispatch).
 template <typename T, int NF, int NTH>
 static void launch_dtt2_typed(const DttArgs<T>& a, hipStream_t s) {
+  if (a.g.periodic[a.axis]) {
+    launch_dtt2<T, NF, NTH, T_DFT>(a, s);
+    return;
+  }
   if constexpr (NF == 128 || NF == 256) {
     const int t0 = a.types[0];
     if (a.types[1] == t0 && a.types[2] == t0) {
@@ -785,7 +799,7 @@ void launch_dtt(const DttArgs<T>& a, int ept, hipStream_t s) {
     launch_dense<T>(a, s);
     return;
   }
-  if (!a.g.periodic[a.axis] && !a.generic) {
+  if (!a.generic) {
     // block size chosen by the host autotuner (a.nt): FP64 128 or 256 threads, FP32 256 or 512
     constexpr int NLO = sizeof(T) == 8 ? 128 : 256;
     constexpr int NHI = sizeof(T) == 8 ? 256 : 512;

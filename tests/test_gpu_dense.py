@@ -64,3 +64,30 @@ def test_static_workspace_without_room_for_matrices():
     x[:, 0] = 0.0
     p, q = a.stage_green(x), b.stage_green(x)
     assert np.abs(p - q).max() <= 1e-12 * np.abs(p).max()
+
+
+PERIODIC = [((16, 100, 104), 0), ((70, 32, 75), 1), ((60, 60, 48), 2), ((64, 5, 3), 0), ((6, 64, 4), 1), ((3, 5, 64), 2),
+            ((96, 3, 6), 0), ((7, 96, 3), 1), ((33, 4, 96), 2), ((128, 4, 3), 0), ((40, 128, 2), 1), ((5, 2, 128), 2),
+            ((256, 2, 3), 0), ((3, 256, 4), 1), ((35, 3, 256), 2)]
+
+
+@pytest.mark.parametrize("idx", range(len(PERIODIC)))
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_green_periodic_compile_time_lengths(idx, prec):
+    """Periodic axes of every length with a compile-time FFT (16, 32 and 48 on grids large enough that
+    they are not taken as matrix products), each axis; tolerances as above."""
+    F = _lib()
+    n, per = PERIODIC[idx]
+    print(f"[periodic green] n={n} periodic={per} prec={prec}", flush=True)
+    rng = np.random.default_rng(800 + idx)
+    lam = rng.uniform(0.3, 3, n[::-1]); mu = rng.uniform(0.2, 2, n[::-1])
+    bc = rng.integers(0, 2, (3, 3, 2)).astype(np.int8)
+    bc[:, per, :] = 2
+    o = OSolver(n, lam, mu, bc, r0_factor=1.2)
+    g = F.Solver(n, lam, mu, bc, r0_factor=1.2, precision=prec)
+    x = rng.standard_normal(o.zeros().shape)
+    x[o.plan.amask] = 0.0
+    ref = o.green.apply(x)
+    out = g.stage_green(x)
+    tol = 1e-12 if prec == "fp64" else 3e-5
+    assert np.abs(out - ref).max() <= tol * np.abs(ref).max()
