@@ -407,6 +407,7 @@ Bufs<T> bufs(fftc_problem* h) {
   B.lam = (const T*)h->lam;
   B.mu = (const T*)h->mu;
   B.mask = h->mask;
+  B.ring = 0;
   return B;
 }
 
@@ -475,7 +476,6 @@ DttArgs<T> dtt_args(fftc_problem* h, int axis, int mode, int force) {
   a.buf = (T*)h->fld[0];
   a.in = (T*)h->fld[0];
   a.B = bufs<T>(h);
-  a.store_s = 0;
   a.st = h->st;
   a.force = force;
   a.cosT = h->cosT;
@@ -520,7 +520,7 @@ DttArgs<float> delta_pass(fftc_problem* h, int p, const DeltaBufs<float>& D) {
 // Green step on the working buffers: u <- DT^-1(M^-1 DT(src)), forward x source chosen by caller
 struct StageTimer;
 template <typename T>
-void enqueue_green(fftc_problem* h, int src, const T* in, int store_s, int force, StageTimer* tm = nullptr);
+void enqueue_green(fftc_problem* h, int src, const T* in, int force, StageTimer* tm = nullptr);
 
 struct StageTimer {
   hipEvent_t ev[16];
@@ -601,6 +601,7 @@ void enqueue_iteration(fftc_problem* h, StageTimer* tm = nullptr, int which = L_
     return;
   }
   Bufs<T> B = bufs<T>(h);
+  B.ring = h->cfg.acv == FFTC_ACV_P;
   const ContactDev ct = contact_dev(h);
   const WeakDev w = weak_dev(h);
   const StrongDev sd = strong_dev(h);
@@ -624,17 +625,16 @@ void enqueue_iteration(fftc_problem* h, StageTimer* tm = nullptr, int which = L_
   if (!(parts & TAIL)) return;
   if (h->cfg.acv == FFTC_ACV_P) launch_anderson<T>(B, n3, h->st, h->gpart, h->nblk_res, which, s);
   if (tm) tm->mark(s);
-  enqueue_green<T>(h, h->cfg.acv == FFTC_ACV_P ? SRC_ANDERSON : SRC_BUF, B.X, h->cfg.acv == FFTC_ACV_P, 0, tm);
+  enqueue_green<T>(h, h->cfg.acv == FFTC_ACV_P ? SRC_ANDERSON : SRC_BUF, B.X, 0, tm);
   launch_proj<T>(h->g, B.u, w, ct, sd, h->st, 1, 0, s);
   if (tm) tm->mark(s);
 }
 
 template <typename T>
-void enqueue_green(fftc_problem* h, int src, const T* in, int store_s, int force, StageTimer* tm) {
+void enqueue_green(fftc_problem* h, int src, const T* in, int force, StageTimer* tm) {
   DttArgs<T> a = dtt_args<T>(h, 0, PASS_FWD, force);
   a.src = src;
   a.in = in;
-  a.store_s = store_s;
   launch_dtt<T>(a, h->ept, h->stream);
   if (tm) tm->mark(h->stream);
   a = dtt_args<T>(h, 1, PASS_FWD, force);
@@ -1022,7 +1022,7 @@ int stage_green_t(fftc_problem* h, const double* ptil_dev, double* u_dev) {
   hipStream_t s = h->stream;
   const long long n3 = 3 * h->Nn;
   launch_convert<double, T>(ptil_dev, B.X, n3, s);
-  enqueue_green<T>(h, SRC_BUF, B.X, 0, 1);
+  enqueue_green<T>(h, SRC_BUF, B.X, 1);
   launch_convert<T, double>(B.u, u_dev, n3, s);
   HIPCHK(h, hipStreamSynchronize(s));
   return FFTC_OK;
@@ -1570,14 +1570,17 @@ int bind_impl(fftc_h h, void* ws, size_t bytes, void* stream, bool tune, bool ma
     hipEventDestroy(e0);
     hipEventDestroy(e1);
   }
-  // occupancy queries of the residual pass instances, outside any capture
-  (void)residual_tiles(h->g, false, false);
-  (void)residual_tiles(h->g, true, false);
-  (void)residual_tiles(h->g, false, true);
-  (void)residual_tiles_fp64(h->g, false);
-  (void)residual_tiles_fp64(h->g, true);
-  (void)residual_tiles_literal<double>(h->g);
-  (void)residual_tiles_literal<float>(h->g);
+  // occupancy queries of the residual pass instances this problem may launch, outside any capture
+  if (h->precision == FFTC_FP64) {
+    (void)residual_tiles_literal<double>(h->g);
+  } else {
+    (void)residual_tiles_literal<float>(h->g);
+    for (int gen = 0; gen < 2; ++gen) {
+      (void)residual_tiles(h->g, gen, false);
+      (void)residual_tiles_fp64(h->g, gen);
+    }
+    (void)residual_tiles(h->g, false, true);
+  }
   if (h->nblk_res >= 8) h->nblk_res -= h->nblk_res % 8;   // whole slabs per XCD
   if (h->nblk_res < 1) h->nblk_res = 1;
   for (int q = 0; q < h->nlit; ++q)

@@ -156,22 +156,22 @@ __global__ __launch_bounds__(256) void k_dense(DttArgs<T> a) {
     }
   };
   if (XL && a.src == SRC_ANDERSON) {
-    const int slot = a.st->i_local & 3, acc_ok = a.st->accel_ok, store_s = a.store_s;
+    const int acc_ok = a.st->accel_ok;
     double al[4] = {0, 0, 0, 0};
     if (acc_ok)
       for (int k = 0; k < 4; ++k) al[k] = a.st->alpha[k];
-    T* Sout = a.B.S[slot] + base;
-    const T* X = a.B.X + base;
+    const T* X = a.B.S[a.st->it & 3] + base;
+    T* Sout = a.B.X + base;
     gather(
         [&](unsigned off, T&) -> T {
           if (!acc_ok) return X[off];
           double s = 0.0;
 #pragma unroll
-          for (int k = 0; k < 4; ++k) s += al[k] * ((double)(a.B.S[k] + base)[off] + (double)(a.B.R[k] + base)[off]);
+          for (int k = 0; k < 4; ++k) s += al[k] * (double)(a.B.S[(k + 1) & 3] + base)[off];
           return (T)s;
         },
         [&](unsigned off, T v, T) {
-          if (store_s) Sout[off] = v;
+          if (acc_ok) Sout[off] = v;
         });
   } else if (XL && a.src == SRC_DELTA) {
     const T* pc = a.dp2[a.st->it & 1] + base;

@@ -319,10 +319,11 @@ __global__ __launch_bounds__(kBlock) void k_dtt(DttArgs<T> a) {
   const int inv_first = (a.mode == PASS_INV);
   {
     const int total = L * N;
-    int slot = 0, acc_ok = 0;
+    int acc_ok = 0;
+    const T* X = nullptr;
     double al[4] = {0, 0, 0, 0};
     if (a.src == SRC_ANDERSON) {
-      slot = a.st->i_local & 3;
+      X = a.B.S[a.st->it & 3];
       acc_ok = a.st->accel_ok;
       if (acc_ok)
         for (int q = 0; q < 4; ++q) al[q] = a.st->alpha[q];
@@ -338,12 +339,12 @@ __global__ __launch_bounds__(kBlock) void k_dtt(DttArgs<T> a) {
           if (acc_ok) {
             double s = 0.0;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) s += al[q] * ((double)a.B.S[q][addr] + (double)a.B.R[q][addr]);
+            for (int q = 0; q < 4; ++q) s += al[q] * (double)a.B.S[(q + 1) & 3][addr];
             v = (T)s;
+            a.B.X[addr] = v;
           } else {
-            v = a.B.X[addr];
+            v = X[addr];
           }
-          if (a.store_s) a.B.S[slot][addr] = v;
         } else if (a.src == SRC_DELTA) {
           v = a.dp2[a.st->it & 1][addr];
           if (a.st->accel_ok) {
@@ -557,30 +558,27 @@ __global__ __launch_bounds__(NTH) void k_dtt2(DttArgs<T> a) {
     });
   };
   if (a.src == SRC_ANDERSON) {
-    const int slot = a.st->i_local & 3;
+    // sum_q alpha_q (S_q + R_q), the fields S_q + R_q being p~ of the four last iterations (128^3:
+    // 143 -> 85 us with four fields read in place of eight; bound by the bytes)
     const int acc_ok = a.st->accel_ok;
-    double al[4] = {0, 0, 0, 0};
-    if (acc_ok)
-      for (int q = 0; q < 4; ++q) al[q] = a.st->alpha[q];
-    T* Sout = a.B.S[slot] + base;
-    const int store_s = a.store_s;
-    const T *S0 = a.B.S[0] + base, *S1 = a.B.S[1] + base, *S2 = a.B.S[2] + base, *S3 = a.B.S[3] + base;
-    const T *R0 = a.B.R[0] + base, *R1 = a.B.R[1] + base, *R2 = a.B.R[2] + base, *R3 = a.B.R[3] + base;
-    const T* X = a.B.X + base;
-    const double al0 = al[0], al1 = al[1], al2 = al[2], al3 = al[3];
+    const double al0 = acc_ok ? a.st->alpha[0] : 0.0, al1 = acc_ok ? a.st->alpha[1] : 0.0,
+                 al2 = acc_ok ? a.st->alpha[2] : 0.0, al3 = acc_ok ? a.st->alpha[3] : 0.0;
+    const T *P0 = a.B.S[1] + base, *P1 = a.B.S[2] + base, *P2 = a.B.S[3] + base, *P3 = a.B.S[0] + base;
+    const T* X = a.B.S[a.st->it & 3] + base;
+    T* Sout = a.B.X + base;
     gather(
         [&](unsigned off, T&) -> T {
           if (acc_ok) {
-            double s = al0 * ((double)S0[off] + (double)R0[off]);
-            s += al1 * ((double)S1[off] + (double)R1[off]);
-            s += al2 * ((double)S2[off] + (double)R2[off]);
-            s += al3 * ((double)S3[off] + (double)R3[off]);
+            double s = al0 * (double)P0[off];
+            s += al1 * (double)P1[off];
+            s += al2 * (double)P2[off];
+            s += al3 * (double)P3[off];
             return (T)s;
           }
           return X[off];
         },
         [&](unsigned off, T v, T) {
-          if (store_s) Sout[off] = v;
+          if (acc_ok) Sout[off] = v;
         });
   } else if (a.src == SRC_DELTA) {
     const T* pcur = a.dp2[a.st->it & 1] + base;

@@ -59,6 +59,7 @@ struct Geo {
 struct DevState {
   int done, status, it, i_local;
   int store_r, accel, accel_ok, acv;
+  int prev_ok, pad0;   // accel_ok of the iteration before (ring: where its input is)
   int have_prev, updates, restarts, vpar;
   int period, max_iter, contact, nC;
   int vnonempty, fine, inc_k, best_it;  // fine: the FP32 form forms stresses in FP64 (sticky);
@@ -139,8 +140,13 @@ template <typename T>
 struct Bufs {
   T* u;        // displacement (also the transform buffer)
   T* X;        // p~ written by the residual pass
-  T* S[4];
+  T* S[4];     // Anderson inputs S_i, R_i = p~_{i+1} - S_i their residuals (slots i mod 4)
   T* R[4];
+  // ACV_P (ring): the residual pass of iteration it writes p~ into S[it mod 4] and S_i is that field,
+  // or X after an accelerating iteration; R_i + S_i is then p~_{i+1}, so that the accelerated
+  // combination reads four fields in place of eight, and a plain iteration stores no input.
+  // R_i is in slot it mod 4 of its iteration.
+  int ring;
   const T* lam;
   const T* mu;
   const uint8_t* mask;
@@ -195,7 +201,6 @@ struct DttArgs {
   T* buf;                      // in/out node-shaped field
   const T* in;                 // forward source when src == SRC_BUF and in != buf
   Bufs<T> B;                   // Anderson buffers (src == SRC_ANDERSON)
-  int store_s;
   DevState* st;
   int force;
   // Green (z pass)

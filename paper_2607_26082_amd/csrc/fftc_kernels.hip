@@ -249,12 +249,18 @@ __device__ __forceinline__ void node_eval_any(const Geo& g, const T* __restrict_
 // ---------------------------------------------------------------------------
 // Residual pass
 // ---------------------------------------------------------------------------
+// field of p~ of the current iteration
+template <typename T>
+__device__ __forceinline__ T* p_field(const Bufs<T>& B, const DevState* st) {
+  return B.ring ? B.S[st->it & 3] : B.X;
+}
+
 // proj_P of the strong conditions and the obstacle at one node of mask m, its part of |p|^2 into pn2,
 // and p (write_p) or p + K0 u into X
 template <typename T>
 __device__ __forceinline__ void residual_tail(const Geo& g, const Bufs<T>& B, const ContactDev& ct, int cur, int i, int j,
                                               int k, long long node, uint8_t m, T p[3], const T k0[3], int write_p,
-                                              double& pn2) {
+                                              T* X, double& pn2) {
   const long long Nn = g.Nn;
   if (ct.on && (m & M_FACE)) {
     const int xyz[3] = {i, j, k};
@@ -285,7 +291,7 @@ __device__ __forceinline__ void residual_tail(const Geo& g, const Bufs<T>& B, co
     }
   }
 #pragma unroll
-  for (int c = 0; c < 3; ++c) B.X[c * Nn + node] = write_p ? p[c] : p[c] + k0[c];
+  for (int c = 0; c < 3; ++c) X[c * Nn + node] = write_p ? p[c] : p[c] + k0[c];
 }
 
 // One node per thread, its neighbours through the caches: HEX1, and node planes wider than
@@ -301,6 +307,7 @@ __global__ __launch_bounds__(kBlock) void k_residual(Geo g, Bufs<T> B, ContactDe
   const int Nx = g.N[0], Ny = g.N[1];
   const long long Nn = g.Nn;
   const int cur = ct.on ? st->vpar : 0;
+  T* const X = p_field(B, st);
   long long lo, hi;
   xcd_chunk(Nn, lo, hi);
   for (long long node = lo + threadIdx.x; node < hi; node += blockDim.x) {
@@ -315,7 +322,7 @@ __global__ __launch_bounds__(kBlock) void k_residual(Geo g, Bufs<T> B, ContactDe
     acc[1] += sn;
 #pragma unroll
     for (int q = 0; q < 6; ++q) acc[2 + q] += ms[q];
-    residual_tail<T>(g, B, ct, cur, i, j, k, node, B.mask[node], p, k0, write_p, acc[0]);
+    residual_tail<T>(g, B, ct, cur, i, j, k, node, B.mask[node], p, k0, write_p, X, acc[0]);
   }
   block_sum<kPartStride>(acc, sh);
   if (threadIdx.x == 0)
@@ -346,6 +353,7 @@ __global__ __launch_bounds__(256) void k_residual_t(Geo g, Bufs<T> B, ContactDev
   const int Nx = g.N[0], Ny = g.N[1], Nz = g.N[2], NxNy = Nx * Ny;
   const int zb = bz * tg.seg, ze = min(zb + tg.seg, Nz);
   const int cur = ct.on ? st->vpar : 0;
+  T* const X = p_field(B, st);
   int off[kPR];
   plane_offsets(g, x0, y0, tid, off);
   T rd[kPR];
@@ -468,7 +476,7 @@ __global__ __launch_bounds__(256) void k_residual_t(Geo g, Bufs<T> B, ContactDev
         p[c] = a ? T(0) : -w2b * F;
         k0[c] = a ? T(0) : Kz[c] + S1[c];
       }
-      residual_tail<T>(g, B, ct, cur, i, j, z, node, m, p, k0, write_p, acc[0]);
+      residual_tail<T>(g, B, ct, cur, i, j, z, node, m, p, k0, write_p, X, acc[0]);
     }
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -525,8 +533,8 @@ __global__ __launch_bounds__(kBlock) void k_weak(Geo g, Bufs<T> B, WeakDev w, De
   const double pnew = (q - wb * f) * scale;
   const double pn = wave_sum(act ? pnew * pnew : 0.0);
   if (act) {
-    const long long e = c * g.Nn + node;
-    B.X[e] = (T)((double)B.X[e] - wb * f * scale);
+    T* X = p_field(B, st) + c * g.Nn + node;
+    *X = (T)((double)*X - wb * f * scale);
   }
   if (lane == 0) {
     w.part[r] = pn;
@@ -727,6 +735,7 @@ __global__ __launch_bounds__(kCtlBlock) void k_control(DevState* st, const doubl
   if (threadIdx.x == 0) {
     st->store_r = (acv == 2) && (i_local > 0);
     st->accel = (acv == 2) && (i_local >= 4) && (i_local % period == 0);
+    st->prev_ok = st->accel_ok;
     st->accel_ok = 0;
   }
 }
@@ -741,17 +750,17 @@ __global__ __launch_bounds__(kBlock) void k_anderson_r(Bufs<T> B, long long n3, 
   if (st->done) return;
   const int store = st->store_r, accel = st->accel;
   if (!store && !accel) return;
-  const int i = st->i_local;
-  const int s = (i + 3) & 3;
+  const int s = ((B.ring ? st->it : st->i_local) + 3) & 3;
   double acc[10];
 #pragma unroll
   for (int q = 0; q < 10; ++q) acc[q] = 0.0;
   T* Rs = B.R[s];
-  const T* Ss = B.S[s];
+  const T* Ss = B.ring && st->prev_ok ? B.X : B.S[s];
+  const T* X = p_field(B, st);
   for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < n3; e += (long long)gridDim.x * blockDim.x) {
     T r[4];
     if (store) {
-      r[s] = B.X[e] - Ss[e];
+      r[s] = X[e] - Ss[e];
       Rs[e] = r[s];
     }
     if (accel) {

@@ -83,3 +83,26 @@ def test_literal_march_at_tile_edges(idx, fs):
     assert np.abs(p - parts["p"]).max() <= 1e-12 * np.abs(parts["p"]).max()
     assert abs(sums[0] - parts["pnorm2"]) <= 1e-11 * parts["pnorm2"]
     assert abs(sums[1] - parts["sig2"]) <= 1e-11 * parts["sig2"]
+
+
+@pytest.mark.parametrize("nx", [14, 16, 260])
+@pytest.mark.parametrize("period", [2, 3])
+def test_accelerated_iterates(nx, period):
+    """The acceleration's ring of iterates under each kernel that combines them (matrix products,
+    compile-time FFT, runtime-length FFT on x): 13 iterations of the FP64 form against the
+    oracle's, every accelerating one among them (2 or 3 apart, so that a combination follows plain
+    iterations of both parities).  1e-9: the iterates' sensitivity to rounding, as in
+    test_gpu_parity.py."""
+    F = _lib()
+    n = (nx, 8, 6)
+    print(f"[accelerated iterates] nx={nx} period={period}", flush=True)
+    rng = np.random.default_rng(1500 + nx)
+    lam = rng.uniform(0.4, 2.5, n[::-1]); mu = rng.uniform(0.3, 1.8, n[::-1])
+    bc = np.zeros((3, 3, 2), np.int8)
+    bc[:, 2, 0] = W.BC_D
+    strong = [W.Strong(np.array([[3, 3, 6], [4, 3, 6]]), np.array([2, 2], np.int8), np.array([0.02, 0.02]))]
+    o = OSolver(n, lam, mu, bc, strong, r0_factor=1.5).solve(tol=1e-14, period=period, max_iter=13)
+    g = F.Solver(n, lam, mu, bc, strong, r0_factor=1.5, precision="fp64", tol=1e-14, period=period, max_iter=13)
+    g.solve()
+    u = g.u.cpu().numpy().reshape(o["u"].shape)
+    assert np.linalg.norm(u - o["u"]) <= 1e-9 * np.linalg.norm(o["u"])
