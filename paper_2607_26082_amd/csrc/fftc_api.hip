@@ -281,6 +281,26 @@ bool dense_axis(const fftc_problem* h, int J) {
          (h->n[J] <= 48 && h->Nn <= 160000 && (h->precision == FFTC_FP32 || h->periodic[J]));
 }
 
+// Whether the passes between the x passes run as one launch, a block per (y, z) plane (k_plane), in place of
+// three.  It pays while the products of a CU's planes stay short: up to 1250 matrix instructions
+// a CU (per iteration, FP64 16^3 54 -> 45 us and 30x22x26 66 -> 58, FP32 64x64x48 95 -> 88; at 1700
+// the other way, FP32 64^3 80 -> 88, and at 1660 in two rounds of planes, 128x48x48 122 -> 128).
+// In FP64 only where the products were taken before or are as exact: on the compile-time lengths
+// 32 and 48 the FFT's error on smooth fields is half that of a product (1e-16 against 2e-16).
+bool plane_route(const fftc_problem* h) {
+  if (h->ref_kind == FFTC_REF_ISO || !(dense_axis(h, 0) || dtt_compiled(h->n[0]))) return false;
+  if (h->precision == FFTC_FP64)
+    for (int J = 1; J < 3; ++J)
+      if (!dense_axis(h, J) && h->n[J] != 16) return false;
+  const int Ny = h->N[1], Nz = h->N[2];
+  const long long ty = (Ny + 15) / 16, tz = (Nz + 15) / 16;
+  const long long steps = 2 * ty * tz * ((Ny + 3) / 4 + (Nz + 3) / 4);   // matrix instructions of a plane
+  return plane_lds(Ny, Nz) <= 64 * 1024 && steps * ((3 * h->N[0] + 255) / 256) <= 1250;
+}
+bool plane_on(const fftc_problem* h) {
+  return plane_route(h) && h->mat[1][h->type[0][1]] != nullptr;
+}
+
 // carve the workspace; with base == nullptr only computes the size.  mats: with the transform
 // matrices (without them every axis runs as FFTs)
 size_t carve(fftc_problem* h, char* base, bool mats = true) {
@@ -337,7 +357,7 @@ size_t carve(fftc_problem* h, char* base, bool mats = true) {
   for (int J = 0; J < 3; ++J)
     for (int t = 0; t < 5; ++t) {
       moff[J][t] = (size_t)-1;
-      if (mats && dense_axis(h, J) && (h->type[0][J] == t || h->type[1][J] == t || h->type[2][J] == t))
+      if (mats && (dense_axis(h, J) || (J > 0 && plane_route(h))) && (h->type[0][J] == t || h->type[1][J] == t || h->type[2][J] == t))
         moff[J][t] = L.take(2 * sizeof(double) * dense_mat_doubles(h->N[J]));
     }
   if (base) {
@@ -485,12 +505,28 @@ DttArgs<T> dtt_args(fftc_problem* h, int axis, int mode, int force) {
   // form); any positive value is at least ~ a theta_min^2, far above this threshold
   for (int c = 0; c < 3; ++c) a.thr[c] = 1e-13 * std::max(h->g.ac[c][0], std::max(h->g.ac[c][1], h->g.ac[c][2]));
   a.nt = h->dtt_nt[pass_of(axis, mode)];
-  for (int c = 0; c < 3; ++c) {
+  for (int c = 0; c < 3 && dense_axis(h, axis); ++c) {
     const double* m = h->mat[axis][h->type[c][axis]];
     a.mat[c][0] = m;
     a.mat[c][1] = m ? m + dense_mat_doubles(h->N[axis]) : nullptr;
   }
+  a.plane = 0;
+  if (plane_on(h)) {
+    // between the x passes the literal forms have a free R slot; the residual form its buffer t
+    a.plane = h->nlit < 10 ? 1 : h->cfg.acv == FFTC_ACV_P ? 2 : 3;
+    a.tr = h->nlit < 10 ? (T*)h->dfld[11] : nullptr;
+  }
   return a;
+}
+
+PlaneMats plane_mats(const fftc_problem* h) {
+  PlaneMats pm;
+  for (int c = 0; c < 3; ++c)
+    for (int d = 0; d < 2; ++d) {
+      pm.y[c][d] = h->mat[1][h->type[c][1]] + d * dense_mat_doubles(h->N[1]);
+      pm.z[c][d] = h->mat[2][h->type[c][2]] + d * dense_mat_doubles(h->N[2]);
+    }
+  return pm;
 }
 
 // Arguments of transform pass p of the FP32 residual-form iteration: the x forward pass forms
@@ -586,8 +622,10 @@ void enqueue_delta_iteration(fftc_problem* h, StageTimer* tm, int which, int par
   if (h->cfg.acv == FFTC_ACV_P && (which & L_ACCEL))
     launch_delta_anderson<float>(D, n3, h->st, h->gpart, h->nblk_res, s);
   if (tm) tm->mark(s);
+  const bool plane = plane_on(h);
   for (int p = 0; p < TP_N; ++p) {
-    launch_dtt<float>(delta_pass(h, p, D), h->ept, s);
+    if (!plane || p == TP_XF || p == TP_XI) launch_dtt<float>(delta_pass(h, p, D), h->ept, s);
+    else if (p == TP_Z) launch_plane<float>(delta_pass(h, p, D), plane_mats(h), s);
     if (tm) tm->mark(s);
   }
   launch_delta_proj<float>(h->g, D, sd, w, ct, h->st, 0, 1, s);
@@ -637,6 +675,15 @@ void enqueue_green(fftc_problem* h, int src, const T* in, int force, StageTimer*
   a.in = in;
   launch_dtt<T>(a, h->ept, h->stream);
   if (tm) tm->mark(h->stream);
+  if (plane_on(h)) {
+    if (tm) tm->mark(h->stream);
+    launch_plane<T>(dtt_args<T>(h, 2, PASS_FWD_GREEN_INV, force), plane_mats(h), h->stream);
+    if (tm) tm->mark(h->stream);
+    if (tm) tm->mark(h->stream);
+    launch_dtt<T>(dtt_args<T>(h, 0, PASS_INV, force), h->ept, h->stream);
+    if (tm) tm->mark(h->stream);
+    return;
+  }
   a = dtt_args<T>(h, 1, PASS_FWD, force);
   launch_dtt<T>(a, h->ept, h->stream);
   if (tm) tm->mark(h->stream);
@@ -1548,7 +1595,9 @@ int bind_impl(fftc_h h, void* ws, size_t bytes, void* stream, bool tune, bool ma
     const int cand[2] = {h->precision == FFTC_FP64 ? 128 : 256, h->precision == FFTC_FP64 ? 256 : 512};
     for (int p = 0; p < TP_N; ++p) {
       h->dtt_nt[p] = cand[1];
-      if (!dtt_compiled(h->n[axis[p]]) || h->mat[axis[p]][h->type[0][axis[p]]]) continue;   // one block size
+      // one block size
+      if (!dtt_compiled(h->n[axis[p]]) || dtt_args<double>(h, axis[p], mode[p], 1).mat[0][0]) continue;
+      if (axis[p] != 0 && plane_on(h)) continue;
       for (int v = 0; v < 2; ++v) {
         h->dtt_nt[p] = cand[v];
         float tot = 0.f;

@@ -189,4 +189,17 @@ __device__ __forceinline__ void svk_pk1(const T (&G)[3][3], T l, T m, T (&P)[3][
 // blocks of kBlock threads for one wavefront per relation
 static inline int rel_grid(long long m) { return (int)((m + (kBlock / 64) - 1) / (kBlock / 64)); }
 
+// Tile of a block: contiguous ranges of tiles per XCD (blocks go to the 8 XCDs round-robin), so that
+// neighbouring tiles share their halo lines in one L2
+__device__ __forceinline__ int xcd_tile(unsigned p, unsigned G) {
+  const unsigned q = G / 8, r = G % 8, xcd = p % 8, slot = p / 8;
+  return (int)(xcd * q + (xcd < r ? xcd : r) + slot);
+}
+
+// field of the transforms between the x passes on the plane route
+template <typename T>
+__device__ __forceinline__ T* plane_field(const DttArgs<T>& a) {
+  return a.plane == 1 ? a.tr : a.B.R[(a.plane == 2 ? a.st->it : a.st->i_local) & 3];
+}
+
 }  // namespace fftc

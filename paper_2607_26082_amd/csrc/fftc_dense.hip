@@ -17,6 +17,7 @@
 // rounding that remains is that of the stored coefficient.
 #include "fftc_internal.h"
 #include "fftc_launch.h"
+#include "fftc_common.h"
 
 #include <math.h>
 #include <algorithm>
@@ -82,7 +83,9 @@ void launch_dense_mats(int type, int n, int N, double* fwd, double* inv, hipStre
 // in FP64.
 // Bound by the chain load - LDS - products - store on small grids (4 to 5 us a pass) and by
 // the FP64 matrix rate on large ones.
-template <typename T, bool XL, bool GREEN, int LT>
+// TO: x lines stored as [x][z][y] (plane route), the roles of the operands exchanged so that 16 lanes
+// hold consecutive y.
+template <typename T, bool XL, bool GREEN, int LT, bool TO = false>
 __global__ __launch_bounds__(256) void k_dense(DttArgs<T> a) {
   extern __shared__ __align__(16) unsigned char smem[];
   if (!a.force && a.st->done) return;
@@ -127,6 +130,10 @@ __global__ __launch_bounds__(256) void k_dense(DttArgs<T> a) {
   const int KS = dense_line_stride(N);
   T* sx = (T*)smem;
   auto at = [&](int l, int k) { return XL ? l * KS + k : k * LB + l; };
+  // plane route: x lines stored to, or read from, [x][z][y]
+  const bool tr_in = XL && a.plane && a.mode == PASS_INV;
+  T* const trf = XL && a.plane ? plane_field(a) + (long long)c * a.g.Nn + (long long)byi * Ny + l0 : nullptr;
+  const int tes = Ny * a.g.N[2];
   auto gather = [&](auto fetch, auto keep) {
     constexpr int U = 8;   // loads in flight per thread
     // element w of the block: x lines node by node, the others line by line
@@ -140,10 +147,11 @@ __global__ __launch_bounds__(256) void k_dense(DttArgs<T> a) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int w = w0 + u * 256;
-        const int l = XL ? (int)(((float)w + 0.5f) * rk) : w % LB;   // w < 2^14: the quotient is exact
-        const int k = XL ? w - l * K : w / LB;
+        const bool by_l = !XL || tr_in;
+        const int l = by_l ? w % LB : (int)(((float)w + 0.5f) * rk);   // w < 2^14: the quotient is exact
+        const int k = by_l ? w / LB : w - l * K;
         ok[u] = w < total && l < nl && k < N;
-        off[u] = (unsigned)(l * ls) + (unsigned)(k * es);
+        off[u] = tr_in ? (unsigned)(l + k * tes) : (unsigned)(l * ls) + (unsigned)(k * es);
         to[u] = w < total ? at(l, k) : -1;
         v[u] = s[u] = T(0);
         if (ok[u]) v[u] = fetch(off[u], s[u]);
@@ -193,7 +201,7 @@ __global__ __launch_bounds__(256) void k_dense(DttArgs<T> a) {
           if (acc_ok) de[off] = k;
         });
   } else {
-    const T* in = a.in + base;
+    const T* in = tr_in ? trf : a.in + base;
     gather([&](unsigned off, T&) -> T { return in[off]; }, [&](unsigned, T, T) {});
   }
   __syncthreads();
@@ -229,8 +237,8 @@ __global__ __launch_bounds__(256) void k_dense(DttArgs<T> a) {
           const double v0 = (double)src[at(16 * u + r, 8 * (kp + i) + q)];
           const double v1 = (double)src[at(16 * u + r, 8 * (kp + i) + 4 + q)];
           d4 &p0 = ps[u][2 * (i & 1)], &p1 = ps[u][2 * (i & 1) + 1];
-          p0 = XL ? mfma64(v0, cur[i].x, p0) : mfma64(cur[i].x, v0, p0);
-          p1 = XL ? mfma64(v1, cur[i].y, p1) : mfma64(cur[i].y, v1, p1);
+          p0 = XL && !TO ? mfma64(v0, cur[i].x, p0) : mfma64(cur[i].x, v0, p0);
+          p1 = XL && !TO ? mfma64(v1, cur[i].y, p1) : mfma64(cur[i].y, v1, p1);
         }
       }
     }
@@ -284,8 +292,13 @@ __global__ __launch_bounds__(256) void k_dense(DttArgs<T> a) {
       for (int u = 0; u < LT; ++u)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const int m = 16 * t + (XL ? r : 4 * e + q), l = 16 * u + (XL ? 4 * e + q : r);
+          constexpr bool LR = XL && !TO;   // D rows are lines
+          const int m = 16 * t + (LR ? r : 4 * e + q), l = 16 * u + (LR ? 4 * e + q : r);
           if (m >= N || l >= nl) continue;
+          if (TO) {
+            trf[l + (long long)m * tes] = (T)acc[u][e];
+            continue;
+          }
           const long long addr = base + (long long)l * ls + (long long)m * es;
           if (!upd) {
             a.buf[addr] = (T)acc[u][e];
@@ -304,14 +317,14 @@ __global__ __launch_bounds__(256) void k_dense(DttArgs<T> a) {
   }
 }
 
-template <typename T, bool XL, bool GREEN, int LT>
+template <typename T, bool XL, bool GREEN, int LT, bool TO = false>
 static void launch_dense_lt(const DttArgs<T>& a, hipStream_t s) {
   const int Nx = a.g.N[0], Ny = a.g.N[1], Nz = a.g.N[2], N = a.ap.N, K = dense_depth(N);
   constexpr int LB = 16 * LT;
   const dim3 grid = XL ? dim3((Ny + LB - 1) / LB, Nz, 3) : dim3((Nx + LB - 1) / LB, a.axis == 1 ? Nz : Ny, 3);
   size_t sm = sizeof(T) * (XL ? (size_t)LB * dense_line_stride(N) : (size_t)K * LB);
   if (GREEN) sm += sizeof(double) * (size_t)K * LB;
-  hipLaunchKernelGGL((k_dense<T, XL, GREEN, LT>), grid, dim3(256), sm, s, a);
+  hipLaunchKernelGGL((k_dense<T, XL, GREEN, LT, TO>), grid, dim3(256), sm, s, a);
 }
 
 template <typename T>
@@ -325,7 +338,10 @@ void launch_dense(const DttArgs<T>& a, hipStream_t s) {
   const size_t sm = a.axis == 0 ? sizeof(T) * 32 * (size_t)dense_line_stride(N)
                                 : (sizeof(T) + (green ? 8 : 0)) * 32 * (size_t)dense_depth(N);
   const bool two = 3 * lines / 16 >= 2048 && sm <= 65536;
-  if (a.axis == 0) {
+  if (a.axis == 0 && a.plane && a.mode == PASS_FWD) {
+    if (two) launch_dense_lt<T, true, false, 2, true>(a, s);
+    else launch_dense_lt<T, true, false, 1, true>(a, s);
+  } else if (a.axis == 0) {
     if (two) launch_dense_lt<T, true, false, 2>(a, s);
     else launch_dense_lt<T, true, false, 1>(a, s);
   } else if (a.mode == PASS_FWD_GREEN_INV) {
@@ -336,6 +352,128 @@ void launch_dense(const DttArgs<T>& a, hipStream_t s) {
     else launch_dense_lt<T, false, false, 1>(a, s);
   }
 }
+
+// --------------------------------------------------------------------------
+// y forward, z forward, symbol, z inverse and y inverse of one (y, z) plane per block
+// --------------------------------------------------------------------------
+// Block (x, component): the plane [z][y] in LDS as FP64, products from one buffer into the other, so
+// that a transform costs one barrier and the three passes one launch and one read and write of
+// the field.  A product unit is one matrix tile against LT tiles of lines.  The x passes lay the
+// field out as [x][z][y] for it (their blocks hold 16 or more y of one z, so both orders are
+// stored in whole sectors).
+// Bound by the chain load - four products, each after a barrier - store: 5 us at 16^3 (y, z and y
+// passes before: 12 us and two gaps), 6 us at 30x22x26, 26 us at 64x64x48 in FP32 (25 and two
+// gaps), where the matrix rate begins to tell.
+template <typename T, int LT>
+__global__ __launch_bounds__(512) void k_plane(DttArgs<T> a, PlaneMats pm) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  if (!a.force && a.st->done) return;
+  const int Ny = a.g.N[1], Nz = a.g.N[2], SY = plane_stride(Ny);
+  const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, wv = tid >> 6, nw = nthr >> 6;
+  const int r = lane & 15, q = lane >> 4;
+  const int b = xcd_tile(blockIdx.x, gridDim.x);
+  const int c = b / a.g.N[0], x = b - c * a.g.N[0];
+  double* P0 = (double*)smem;
+  double* P1 = P0 + (size_t)Nz * SY;
+  T* f = plane_field(a) + (long long)c * a.g.Nn + (long long)x * Ny * Nz;
+  const float ry = 1.0f / (float)Ny;
+  const int total = Ny * Nz;
+  constexpr int U = 4;
+  for (int w0 = tid; w0 < total; w0 += U * nthr) {
+    T v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = w0 + u * nthr < total ? f[w0 + u * nthr] : T(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int w = w0 + u * nthr;
+      if (w >= total) continue;
+      const int z = (int)(((float)w + 0.5f) * ry);   // w < 2^15: the quotient is exact
+      P0[z * SY + (w - z * Ny)] = (double)v[u];
+    }
+  }
+  // transform along an axis of length N and element stride sk, its M lines sl apart; put(m, l, value)
+  auto pass = [&](const double* mat, const double* src, int N, int sk, int M, int sl, auto put) {
+    const int nt = (N + 15) / 16, np = dense_depth(N) / 8, nu = (M + 16 * LT - 1) / (16 * LT);
+    __syncthreads();
+    for (int unit = wv; unit < nt * nu; unit += nw) {
+      const int t = unit / nu, u0 = (unit - t * nu) * 16 * LT;
+      const double2* mp = (const double2*)mat + (size_t)t * np * 64 + lane;
+      const double* ln[LT];
+#pragma unroll
+      for (int u = 0; u < LT; ++u) ln[u] = src + min(u0 + 16 * u + r, M - 1) * sl;
+      // four partial sums per output, as in k_dense
+      d4 ps[LT][4];
+#pragma unroll
+      for (int u = 0; u < LT; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ps[u][i] = d4{0.0, 0.0, 0.0, 0.0};
+      constexpr int kU = 4;
+      double2 nxt[kU];
+#pragma unroll
+      for (int i = 0; i < kU; ++i) nxt[i] = i < np ? mp[(size_t)i * 64] : make_double2(0.0, 0.0);
+      for (int kp = 0; kp < np; kp += kU) {
+        double2 cur[kU];
+#pragma unroll
+        for (int i = 0; i < kU; ++i) {
+          cur[i] = nxt[i];
+          if (kp + kU + i < np) nxt[i] = mp[(size_t)(kp + kU + i) * 64];
+        }
+#pragma unroll
+        for (int i = 0; i < kU; ++i) {
+          if (kp + i >= np) break;
+          // (beyond the line the matrix is 0: any finite value of the line serves)
+          const int k0 = min(8 * (kp + i) + q, N - 1) * sk, k1 = min(8 * (kp + i) + 4 + q, N - 1) * sk;
+#pragma unroll
+          for (int u = 0; u < LT; ++u) {
+            ps[u][2 * (i & 1)] = mfma64(cur[i].x, ln[u][k0], ps[u][2 * (i & 1)]);
+            ps[u][2 * (i & 1) + 1] = mfma64(cur[i].y, ln[u][k1], ps[u][2 * (i & 1) + 1]);
+          }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < LT; ++u) {
+        const d4 acc = (ps[u][0] + ps[u][1]) + (ps[u][2] + ps[u][3]);
+        const int l = u0 + 16 * u + r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int m = 16 * t + 4 * e + q;
+          if (m < N && l < M) put(m, l, acc[e]);
+        }
+      }
+    }
+  };
+  pass(pm.y[c][0], P0, Ny, 1, Nz, SY, [&](int m, int l, double v) { P1[l * SY + m] = v; });
+  const double* tab = a.cosT + (size_t)c * 6 * a.maxN;
+  const double a0 = a.g.ac[c][0], a1 = a.g.ac[c][1], a2 = a.g.ac[c][2], hx = a.g.hex ? 0.0 : 1.0;
+  const double sx = tab[x], qx = tab[a.maxN + x], thr = a.thr[c];
+  pass(pm.z[c][0], P1, Nz, SY, Ny, 1, [&](int m, int l, double v) {
+    // the factored Paux symbol (paux_symbol of the FFT passes)
+    const double sy = tab[2 * a.maxN + l], qy = tab[3 * a.maxN + l];
+    const double A = 4.0 * (a0 * sx * qy + a1 * sy * qx + hx * a2 * sx * sy);
+    const double B = 4.0 * (hx * a0 * qx * sy + hx * a1 * qy * sx + a2 * qx * qy);
+    const double S = tab[5 * a.maxN + m] * A + tab[4 * a.maxN + m] * B;
+    P0[m * SY + l] = S > thr ? v / S : 0.0;
+  });
+  pass(pm.z[c][1], P0, Nz, SY, Ny, 1, [&](int m, int l, double v) { P1[m * SY + l] = v; });
+  pass(pm.y[c][1], P1, Ny, 1, Nz, SY, [&](int m, int l, double v) { P0[l * SY + m] = v; });
+  __syncthreads();
+  for (int w = tid; w < total; w += nthr) {
+    const int z = (int)(((float)w + 0.5f) * ry);
+    f[w] = (T)P0[z * SY + (w - z * Ny)];
+  }
+}
+
+template <typename T>
+void launch_plane(const DttArgs<T>& a, const PlaneMats& pm, hipStream_t s) {
+  const int Ny = a.g.N[1], Nz = a.g.N[2];
+  const size_t sm = plane_lds(Ny, Nz);
+  const int tiles = ((Ny + 15) / 16) * ((Nz + 15) / 16);
+  const dim3 grid(3 * a.g.N[0]), block(tiles <= 4 ? 256 : 512);
+  if (tiles <= 9) hipLaunchKernelGGL((k_plane<T, 1>), grid, block, sm, s, a, pm);
+  else hipLaunchKernelGGL((k_plane<T, 2>), grid, block, sm, s, a, pm);
+}
+template void launch_plane<float>(const DttArgs<float>&, const PlaneMats&, hipStream_t);
+template void launch_plane<double>(const DttArgs<double>&, const PlaneMats&, hipStream_t);
 
 template void launch_dense<float>(const DttArgs<float>&, hipStream_t);
 template void launch_dense<double>(const DttArgs<double>&, hipStream_t);

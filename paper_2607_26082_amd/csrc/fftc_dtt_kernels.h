@@ -518,14 +518,18 @@ __global__ __launch_bounds__(NTH) void k_dtt2(DttArgs<T> a) {
   };
   // the element loops are compiled once per ownership map (axis is uniform), so that the
   // fixed line or node of a thread is loop-invariant
+  // plane route: x lines stored to, or read from, [x][z][y]
+  const bool tr_in = a.plane && a.mode == PASS_INV, tr_out = a.plane && a.mode == PASS_FWD;
+  T* const trf = a.plane ? plane_field(a) + (long long)c * a.g.Nn + (long long)byi * Ny + (long long)bxi * LB : nullptr;
   auto by_map = [&](auto&& f) {
-    if (axis != 0) f(std::integral_constant<int, 1>{});
+    if (axis != 0 || tr_in) f(std::integral_constant<int, 1>{});
     else f(std::integral_constant<int, 0>{});
   };
-  const unsigned ls = (unsigned)lstride, es = (unsigned)estride;
+  const unsigned ls = (unsigned)lstride, es = (unsigned)estride, tes = (unsigned)(Ny * a.g.N[2]);
+  const unsigned lsi = tr_in ? 1u : ls, esi = tr_in ? tes : es, lso = tr_out ? 1u : ls, eso = tr_out ? tes : es;
   const bool has_tail = !PER && tid < (unsigned)LB;
   const bool tail_ok = has_tail && (int)tid < nl;
-  const unsigned tail_off = tid * ls + (unsigned)NF * es;
+  const unsigned tail_off = tid * ls + (unsigned)NF * es, tail_in = tid * lsi + (unsigned)NF * esi;
   // gather the real lines into LDS: all loads of a thread are issued before any store (the
   // stores of S or c would otherwise hold back the next loads: the pointers may alias).
   // fetch(off, k) returns the value to transform and sets k, the value keep(off, v, k) may store.
@@ -537,17 +541,17 @@ __global__ __launch_bounds__(NTH) void k_dtt2(DttArgs<T> a) {
         unsigned l, m;
         body(mk, i, l, m);
         kv[i] = T(0);
-        vals[i] = ((int)l < nl) ? fetch(l * ls + m * es, kv[i]) : T(0);
+        vals[i] = ((int)l < nl) ? fetch(l * lsi + m * esi, kv[i]) : T(0);
       }
       kv[NB] = T(0);
-      vals[NB] = tail_ok ? fetch(tail_off, kv[NB]) : T(0);
+      vals[NB] = tail_ok ? fetch(tail_in, kv[NB]) : T(0);
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         unsigned l, m;
         body(mk, i, l, m);
-        if ((int)l < nl) keep(l * ls + m * es, vals[i], kv[i]);
+        if ((int)l < nl) keep(l * lsi + m * esi, vals[i], kv[i]);
       }
-      if (tail_ok) keep(tail_off, vals[NB], kv[NB]);
+      if (tail_ok) keep(tail_in, vals[NB], kv[NB]);
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         unsigned l, m;
@@ -622,7 +626,7 @@ __global__ __launch_bounds__(NTH) void k_dtt2(DttArgs<T> a) {
           });
     }
   } else {
-    const T* in = a.in + base;
+    const T* in = tr_in ? trf : a.in + base;
     gather([&](unsigned off, T&) -> T { return in[off]; }, [&](unsigned, T, T) {});
   }
   __syncthreads();
@@ -733,7 +737,7 @@ __global__ __launch_bounds__(NTH) void k_dtt2(DttArgs<T> a) {
     else update(std::integral_constant<int, 0>{}, std::true_type{});
     return;
   }
-  T* out = a.buf + base;
+  T* out = tr_out ? trf : a.buf + base;
   // guarded: some lines of the block lie beyond the grid (last chunk only); x lines of a
   // full block take the unguarded copy, where the thread's fixed node is loop-invariant
   auto store = [&](auto mk, auto guarded) {
@@ -742,13 +746,13 @@ __global__ __launch_bounds__(NTH) void k_dtt2(DttArgs<T> a) {
       unsigned l, m;
       body(mk, i, l, m);
       const T v = post(inv_out, cb + l * CS, m);
-      if (!decltype(guarded)::value || (int)l < nl) out[l * ls + m * es] = v;
+      if (!decltype(guarded)::value || (int)l < nl) out[l * lso + m * eso] = v;
     }
   };
-  if (axis != 0) store(std::integral_constant<int, 1>{}, std::true_type{});
+  if (axis != 0 || tr_out) store(std::integral_constant<int, 1>{}, std::true_type{});
   else if (nl >= LB) store(std::integral_constant<int, 0>{}, std::false_type{});
   else store(std::integral_constant<int, 0>{}, std::true_type{});
-  if (tail_ok) out[tail_off] = post(inv_out, cb + tid * CS, NF);
+  if (tail_ok) out[tid * lso + (unsigned)NF * eso] = post(inv_out, cb + tid * CS, NF);
 }
 
 template <typename T>

@@ -127,6 +127,16 @@ inline bool dtt_compiled(int n) {
   return n == 16 || n == 32 || n == 48 || n == 64 || n == 96 || n == 128 || n == 256;
 }
 
+// LDS of a plane of the plane route: two FP64 buffers, rows an odd number of values apart (16 lanes
+// reading the same y of 16 rows meet distinct banks)
+__host__ __device__ inline int plane_stride(int Ny) { return Ny | 1; }
+inline size_t plane_lds(int Ny, int Nz) { return 2 * sizeof(double) * (size_t)Nz * plane_stride(Ny); }
+// forward and inverse matrices of the y and z axes per component
+struct PlaneMats {
+  const double* y[3][2];
+  const double* z[3][2];
+};
+
 // Matrix passes (fftc_dense.hip): depth of the products for N nodes (a multiple of 8), doubles of one
 // transform matrix, and the LDS stride of an x line (at least the depth, and 4 mod 32: see k_dense)
 __host__ __device__ inline int dense_depth(int N) { return (N + 7) / 8 * 8; }
@@ -211,6 +221,11 @@ struct DttArgs {
   double thr[3];
   int generic;                 // force the runtime-length kernel
   int nt;                      // threads per block of the compile-time-length kernel
+  // Plane route (k_plane): the x forward pass leaves every component as [x][z][y] in the field below,
+  // the x inverse pass reads it there.  0: not taken; 1: in tr; 2, 3: in the R slot that the
+  // next iteration will overwrite (slots by it, by i_local)
+  int plane;
+  T* tr;
   const double* mat[3][2];     // per component forward and inverse matrix (matrix passes), or null
   // residual-form (FP32) iteration
   int dst;                     // DST_BUF or DST_UPDATE (x inverse pass: delta and FP64 u update)

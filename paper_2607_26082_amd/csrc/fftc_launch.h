@@ -61,6 +61,9 @@ template <typename T>
 size_t dtt_smem(const AxisPlan& ap);
 template <typename T>
 void launch_dtt(const DttArgs<T>& a, int ept, hipStream_t s);
+// the passes between the x passes on the plane route
+template <typename T>
+void launch_plane(const DttArgs<T>& a, const PlaneMats& pm, hipStream_t s);
 template <typename T>
 void launch_dense(const DttArgs<T>& a, hipStream_t s);
 void launch_dense_mats(int type, int n, int N, double* fwd, double* inv, hipStream_t s);

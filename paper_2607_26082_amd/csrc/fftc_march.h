@@ -28,13 +28,6 @@ constexpr int kPR = (kPlane + 255) / 256;     // of them per thread
 int resident_blocks(const void* kernel, std::atomic<int> (&cache)[64]);
 TileGrid tile_grid_for(const Geo& g, int resident);
 
-// Tile of a block: contiguous ranges of tiles per XCD (blocks go to the 8 XCDs round-robin), so that
-// neighbouring tiles share their halo lines in one L2
-__device__ __forceinline__ int xcd_tile(unsigned p, unsigned G) {
-  const unsigned q = G / 8, r = G % 8, xcd = p % 8, slot = p / 8;
-  return (int)(xcd * q + (xcd < r ? xcd : r) + slot);
-}
-
 // slot of node plane pz (>= -1) in a ring of three
 __device__ __forceinline__ int ring3(int pz) { return (pz + 3) % 3; }
 

@@ -91,3 +91,32 @@ def test_green_periodic_compile_time_lengths(idx, prec):
     out = g.stage_green(x)
     tol = 1e-12 if prec == "fp64" else 3e-5
     assert np.abs(out - ref).max() <= tol * np.abs(ref).max()
+
+
+PLANES = [((16, 16, 16), None), ((14, 15, 16), None), ((16, 14, 15), None), ((32, 30, 33), None), ((15, 48, 48), None),
+          ((64, 64, 48), None), ((48, 39, 50), None), ((5, 2, 2), None), ((2, 65, 2), None), ((6, 2, 180), None),
+          ((260, 14, 15), None), ((16, 16, 14), 1), ((14, 15, 16), 2), ((16, 13, 14), 0), ((96, 24, 22), None)]
+
+
+@pytest.mark.parametrize("idx", range(len(PLANES)))
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_green_on_planes(idx, prec):
+    """Small (y, z) planes, whose transforms between the x passes are one launch: edges of the 16-wide
+    tiles, one and two line tiles per unit, both kinds of x pass next to it (and one that it is not
+    taken with), planes of two nodes, periodic axes.  Tolerances as above."""
+    F = _lib()
+    n, per = PLANES[idx]
+    print(f"[plane green] n={n} periodic={per} prec={prec}", flush=True)
+    rng = np.random.default_rng(1100 + idx)
+    lam = rng.uniform(0.3, 3, n[::-1]); mu = rng.uniform(0.2, 2, n[::-1])
+    bc = rng.integers(0, 2, (3, 3, 2)).astype(np.int8)
+    if per is not None:
+        bc[:, per, :] = 2
+    o = OSolver(n, lam, mu, bc, r0_factor=1.2)
+    g = F.Solver(n, lam, mu, bc, r0_factor=1.2, precision=prec)
+    x = rng.standard_normal(o.zeros().shape)
+    x[o.plan.amask] = 0.0
+    ref = o.green.apply(x)
+    out = g.stage_green(x)
+    tol = 1e-12 if prec == "fp64" else 3e-5
+    assert np.abs(out - ref).max() <= tol * np.abs(ref).max()
