@@ -282,9 +282,9 @@ bool dense_axis(const fftc_problem* h, int J) {
 }
 
 // Whether the passes between the x passes run as one launch, a block per (y, z) plane (k_plane), in place of
-// three.  It pays while the products of a CU's planes stay short: up to 1250 matrix instructions
-// a CU (per iteration, FP64 16^3 54 -> 45 us and 30x22x26 66 -> 58, FP32 64x64x48 95 -> 88; at 1700
-// the other way, FP32 64^3 80 -> 88, and at 1660 in two rounds of planes, 128x48x48 122 -> 128).
+// three.  It pays while the products of a CU's planes stay short: up to 900 matrix instructions a CU
+// (per iteration, FP64 16^3 54 -> 45 us and 30x22x26 66 -> 58; at 1200 the other way, FP32 64x64x48
+// 87 -> 89).
 // In FP64 only where the products were taken before or are as exact: on the compile-time lengths
 // 32 and 48 the FFT's error on smooth fields is half that of a product (1e-16 against 2e-16).
 bool plane_route(const fftc_problem* h) {
@@ -295,7 +295,7 @@ bool plane_route(const fftc_problem* h) {
   const int Ny = h->N[1], Nz = h->N[2];
   const long long ty = (Ny + 15) / 16, tz = (Nz + 15) / 16;
   const long long steps = 2 * ty * tz * ((Ny + 3) / 4 + (Nz + 3) / 4);   // matrix instructions of a plane
-  return plane_lds(Ny, Nz) <= 64 * 1024 && steps * ((3 * h->N[0] + 255) / 256) <= 1250;
+  return plane_lds(Ny, Nz) <= 64 * 1024 && steps * ((3 * h->N[0] + 255) / 256) <= 900;
 }
 bool plane_on(const fftc_problem* h) {
   return plane_route(h) && h->mat[1][h->type[0][1]] != nullptr;

@@ -362,8 +362,8 @@ void launch_dense(const DttArgs<T>& a, hipStream_t s) {
 // field out as [x][z][y] for it (their blocks hold 16 or more y of one z, so both orders are
 // stored in whole sectors).
 // Bound by the chain load - four products, each after a barrier - store: 5 us at 16^3 (y, z and y
-// passes before: 12 us and two gaps), 6 us at 30x22x26, 26 us at 64x64x48 in FP32 (25 and two
-// gaps), where the matrix rate begins to tell.
+// passes before: 12 us and two gaps), 6 us at 30x22x26 (10 and two gaps), 17 us at 48^3 in FP32 (18 and
+// two gaps), where the matrix rate begins to tell.
 template <typename T, int LT>
 __global__ __launch_bounds__(512) void k_plane(DttArgs<T> a, PlaneMats pm) {
   extern __shared__ __align__(16) unsigned char smem[];

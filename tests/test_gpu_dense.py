@@ -120,3 +120,30 @@ def test_green_on_planes(idx, prec):
     out = g.stage_green(x)
     tol = 1e-12 if prec == "fp64" else 3e-5
     assert np.abs(out - ref).max() <= tol * np.abs(ref).max()
+
+
+QUARTER = [((18, 22, 16), 0), ((70, 54, 48), 1), ((130, 33, 32), 0), ((3, 5, 64), 1), ((65, 3, 64), 0), ((18, 4, 96), 0),
+           ((64, 2, 96), 1), ((33, 3, 128), 0), ((5, 2, 128), 1), ((15, 3, 256), 0), ((32, 2, 256), 1)]
+
+
+@pytest.mark.parametrize("idx", range(len(QUARTER)))
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_green_quarter_wave_z_lines(idx, prec):
+    """z lines fixed at one end in every component (DCT3 or DST3), which share an FFT in pairs: each
+    compile-time length, full and partial blocks of lines and a second line beyond the grid.
+    Tolerances as above."""
+    F = _lib()
+    n, end = QUARTER[idx]
+    print(f"[quarter green] n={n} fixed end={end} prec={prec}", flush=True)
+    rng = np.random.default_rng(1200 + idx)
+    lam = rng.uniform(0.3, 3, n[::-1]); mu = rng.uniform(0.2, 2, n[::-1])
+    bc = rng.integers(0, 2, (3, 3, 2)).astype(np.int8)
+    bc[:, 2, end], bc[:, 2, 1 - end] = 1, 0
+    o = OSolver(n, lam, mu, bc, r0_factor=1.2)
+    g = F.Solver(n, lam, mu, bc, r0_factor=1.2, precision=prec)
+    x = rng.standard_normal(o.zeros().shape)
+    x[o.plan.amask] = 0.0
+    ref = o.green.apply(x)
+    out = g.stage_green(x)
+    tol = 1e-12 if prec == "fp64" else 3e-5
+    assert np.abs(out - ref).max() <= tol * np.abs(ref).max()
