@@ -520,74 +520,107 @@ void k_residual_dt(Geo g, DeltaBufs<T> D, ContactDev ct, DevState* st, double* _
 // FP64 displacement against corner 000, rounded to T; the stress arithmetic in T), added in T
 // and weighted by the integration-point weight 1/2 into FP64 block sums.  Components in the
 // order xx, yy, zz, yz, xz, xy (first Piola-Kirchhoff for finite strain).
+// A thread owns a column of voxels over a segment of z: the upper corners of a layer are the
+// lower ones of the next (12 loads a voxel, requested a layer ahead), and nothing is divided.
+// Bound by the 540 MB and the loads in flight: 256^3 181 us (one voxel per thread and step, with 24
+// loads and three 64-bit divisions: 290 us).
+constexpr int kMSX = 64, kMSY = kBlock / kMSX;
 template <typename T, bool FS>
 __global__ __launch_bounds__(kBlock) void k_mean_stress_d(Geo g, const double* __restrict__ u,
                                                           const T* __restrict__ lam, const T* __restrict__ mu,
-                                                          double* __restrict__ part) {
+                                                          double* __restrict__ part, int tx, int ty, int seg) {
   __shared__ double sh[6 * 16];
   double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  const int nx = g.n[0], ny = g.n[1];
-  const long long Nn = g.Nn;
-  long long lo, hi;
-  xcd_chunk(g.Nv, lo, hi);
-  for (long long v = lo + threadIdx.x; v < hi; v += blockDim.x) {
-    const int vx = (int)(v % nx);
-    const long long r = v / nx;
-    const int vy = (int)(r % ny), vz = (int)(r / ny);
-    double uc[8][3];
+  const int nx = g.n[0], ny = g.n[1], Nx = g.N[0], NxNy = g.N[0] * g.N[1];
+  const int units = tx * ty * ((g.n[2] + seg - 1) / seg), per = (units + gridDim.x - 1) / gridDim.x;
+  const int first = xcd_tile(blockIdx.x, gridDim.x) * per;
+  for (int b = first; b < min(first + per, units); ++b) {
+    const int vx = (b % tx) * kMSX + (int)threadIdx.x % kMSX, vy = (b / tx) % ty * kMSY + (int)threadIdx.x / kMSX;
+    const int zb = b / (tx * ty) * seg, ze = vx < nx && vy < ny ? min(zb + seg, g.n[2]) : zb;
+    int at[4];   // corners (0,0), (1,0), (0,1), (1,1) in a plane (on a periodic axis there are n nodes)
 #pragma unroll
-    for (int cc = 0; cc < 8; ++cc) {
-      int x = vx + (cc & 1), y = vy + ((cc >> 1) & 1), z = vz + ((cc >> 2) & 1);
-      if (x == g.N[0]) x = 0;   // only on a periodic axis, where there are n nodes
-      if (y == g.N[1]) y = 0;
-      if (z == g.N[2]) z = 0;
-      const long long node = (long long)x + (long long)g.N[0] * ((long long)y + (long long)g.N[1] * z);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) uc[cc][c] = u[c * Nn + node];
+    for (int q = 0; q < 4; ++q) {
+      const int x = vx + (q & 1), y = vy + (q >> 1);
+      at[q] = (x == g.N[0] ? 0 : x) + Nx * (y == g.N[1] ? 0 : y);
     }
-    const T l = lam[v], m = mu[v];
-    T vs[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
+    double nxt[4][3], uc[8][3];
+    auto fetch = [&](int z) {
+      const double* pl = u + (long long)NxNy * (z == g.N[2] ? 0 : z);
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      T G[3][3];
+      for (int c = 0; c < 3; ++c)
 #pragma unroll
-      for (int a = 0; a < 3; ++a)
+        for (int q = 0; q < 4; ++q) nxt[q][c] = pl[c * g.Nn + at[q]];
+    };
+    auto take = [&](int h) {
 #pragma unroll
-        for (int b = 0; b < 3; ++b) G[a][b] = T(0);
+      for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int cc = 1; cc < 8; ++cc) {
-        const int cx = cc & 1, cy = (cc >> 1) & 1, cz = (cc >> 2) & 1;
-        if (((cx + cy + cz) & 1) != t) continue;
-        const T sx = T(cx ? 0.5 : -0.5), sy = T(cy ? 0.5 : -0.5), sz = T(cz ? 0.5 : -0.5);
+        for (int c = 0; c < 3; ++c) uc[h + q][c] = nxt[q][c];
+    };
+    T l = T(0), m = T(0);
+    const int col = vx + nx * vy, nxny = nx * ny;
+    if (zb < ze) {
+      fetch(zb);
+      take(4);
+      fetch(zb + 1);
+      l = lam[col + nxny * zb];
+      m = mu[col + nxny * zb];
+    }
+    for (int vz = zb; vz < ze; ++vz) {
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          const T d = (T)(uc[cc][a] - uc[0][a]);
-          G[a][0] += sx * d;
-          G[a][1] += sy * d;
-          G[a][2] += sz * d;
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) uc[q][c] = uc[4 + q][c];
+      take(4);
+      const T l0 = l, m0 = m;
+      if (vz + 1 < ze) {
+        fetch(vz + 2);
+        l = lam[col + nxny * (vz + 1)];
+        m = mu[col + nxny * (vz + 1)];
+      }
+      T vs[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        T G[3][3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+          for (int b = 0; b < 3; ++b) G[a][b] = T(0);
+#pragma unroll
+        for (int cc = 1; cc < 8; ++cc) {
+          const int cx = cc & 1, cy = (cc >> 1) & 1, cz = (cc >> 2) & 1;
+          if (((cx + cy + cz) & 1) != t) continue;
+          const T sx = T(cx ? 0.5 : -0.5), sy = T(cy ? 0.5 : -0.5), sz = T(cz ? 0.5 : -0.5);
+#pragma unroll
+          for (int a = 0; a < 3; ++a) {
+            const T d = (T)(uc[cc][a] - uc[0][a]);
+            G[a][0] += sx * d;
+            G[a][1] += sy * d;
+            G[a][2] += sz * d;
+          }
+        }
+        if constexpr (FS) {
+          T P[3][3];
+          svk_pk1<T>(G, l0, m0, P);
+          vs[0] += P[0][0];
+          vs[1] += P[1][1];
+          vs[2] += P[2][2];
+          vs[3] += P[1][2];
+          vs[4] += P[0][2];
+          vs[5] += P[0][1];
+        } else {
+          const T tr = G[0][0] + G[1][1] + G[2][2];
+          vs[0] += l0 * tr + T(2) * m0 * G[0][0];
+          vs[1] += l0 * tr + T(2) * m0 * G[1][1];
+          vs[2] += l0 * tr + T(2) * m0 * G[2][2];
+          vs[3] += m0 * (G[1][2] + G[2][1]);
+          vs[4] += m0 * (G[0][2] + G[2][0]);
+          vs[5] += m0 * (G[0][1] + G[1][0]);
         }
       }
-      if constexpr (FS) {
-        T P[3][3];
-        svk_pk1<T>(G, l, m, P);
-        vs[0] += P[0][0];
-        vs[1] += P[1][1];
-        vs[2] += P[2][2];
-        vs[3] += P[1][2];
-        vs[4] += P[0][2];
-        vs[5] += P[0][1];
-      } else {
-        const T tr = G[0][0] + G[1][1] + G[2][2];
-        vs[0] += l * tr + T(2) * m * G[0][0];
-        vs[1] += l * tr + T(2) * m * G[1][1];
-        vs[2] += l * tr + T(2) * m * G[2][2];
-        vs[3] += m * (G[1][2] + G[2][1]);
-        vs[4] += m * (G[0][2] + G[2][0]);
-        vs[5] += m * (G[0][1] + G[1][0]);
-      }
-    }
 #pragma unroll
-    for (int q = 0; q < 6; ++q) acc[q] += 0.5 * (double)vs[q];
+      for (int q = 0; q < 6; ++q) acc[q] += 0.5 * (double)vs[q];
+    }
   }
   block_sum<6>(acc, sh);
   if (threadIdx.x == 0)
@@ -872,9 +905,14 @@ void launch_diff(const T* a, const T* b, T* out, long long n, hipStream_t s) {
 
 template <typename T>
 int launch_mean_stress_d(const Geo& g, const DeltaBufs<T>& D, double* part, hipStream_t s) {
-  const int nblk = (int)std::max<long long>(1, std::min<long long>(1024, (g.Nv + kBlock - 1) / kBlock));
-  if (g.fs) hipLaunchKernelGGL((k_mean_stress_d<T, true>), dim3(nblk), dim3(kBlock), 0, s, g, D.u, D.lam, D.mu, part);
-  else hipLaunchKernelGGL((k_mean_stress_d<T, false>), dim3(nblk), dim3(kBlock), 0, s, g, D.u, D.lam, D.mu, part);
+  // segments of z for up to 1024 blocks (four a CU)
+  const int tx = (g.n[0] + kMSX - 1) / kMSX, ty = (g.n[1] + kMSY - 1) / kMSY;
+  const int want = std::max(1, std::min(g.n[2], 1024 / std::max(1, tx * ty)));
+  const int seg = (g.n[2] + want - 1) / want;
+  const int nblk = std::min(1024, tx * ty * ((g.n[2] + seg - 1) / seg));
+  const dim3 grid(nblk), block(kBlock);
+  if (g.fs) hipLaunchKernelGGL((k_mean_stress_d<T, true>), grid, block, 0, s, g, D.u, D.lam, D.mu, part, tx, ty, seg);
+  else hipLaunchKernelGGL((k_mean_stress_d<T, false>), grid, block, 0, s, g, D.u, D.lam, D.mu, part, tx, ty, seg);
   return nblk;
 }
 
