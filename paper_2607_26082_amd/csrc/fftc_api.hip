@@ -1583,7 +1583,11 @@ int bind_impl(fftc_h h, void* ws, size_t bytes, void* stream, bool tune, bool ma
   // iteration runs it (the FP32 form's x passes with their residual-form source and FP64
   // update), on the bound buffers with a cleared state (no acceleration, nothing done)
   if (!tune) {
-    for (int p = 0; p < TP_N; ++p) h->dtt_nt[p] = h->precision == FFTC_FP64 ? 256 : 512;
+    static const int ax[TP_N] = {0, 1, 2, 1, 0};
+    for (int p = 0; p < TP_N; ++p) {
+      const int lo = dtt_threads(h->precision == FFTC_FP64, h->n[ax[p]]);
+      h->dtt_nt[p] = h->n[ax[p]] == 256 ? 2 * lo : lo;
+    }
   } else {
     HIPCHK(h, hipMemsetAsync(h->st, 0, sizeof(DevState), s));
     const bool delta = h->precision == FFTC_FP32 && h->nlit < 10;   // runs the residual form
@@ -1592,8 +1596,8 @@ int bind_impl(fftc_h h, void* ws, size_t bytes, void* stream, bool tune, bool ma
     hipEvent_t e0, e1;
     HIPCHK(h, hipEventCreate(&e0));
     HIPCHK(h, hipEventCreate(&e1));
-    const int cand[2] = {h->precision == FFTC_FP64 ? 128 : 256, h->precision == FFTC_FP64 ? 256 : 512};
     for (int p = 0; p < TP_N; ++p) {
+      const int lo = dtt_threads(h->precision == FFTC_FP64, h->n[axis[p]]), cand[2] = {lo, 2 * lo};
       h->dtt_nt[p] = cand[1];
       // one block size
       if (!dtt_compiled(h->n[axis[p]]) || dtt_args<double>(h, axis[p], mode[p], 1).mat[0][0]) continue;

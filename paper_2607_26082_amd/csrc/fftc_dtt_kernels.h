@@ -925,15 +925,14 @@ void launch_dtt(const DttArgs<T>& a, int ept, hipStream_t s) {
     return;
   }
   if (!a.generic) {
-    // block size chosen by the host autotuner (a.nt): FP64 128 or 256 threads, FP32 256 or 512
-    constexpr int NLO = sizeof(T) == 8 ? 128 : 256;
-    constexpr int NHI = sizeof(T) == 8 ? 256 : 512;
-    const bool hi = a.nt >= NHI;
-#define FFTC_DTT_CASE(L)                                   \
-  case L:                                                  \
-    if (hi) launch_dtt2_typed<T, L, NHI>(a, s);            \
-    else launch_dtt2_typed<T, L, NLO>(a, s);               \
-    return;
+    // block size chosen by the host autotuner (a.nt, one of dtt_threads)
+#define FFTC_DTT_CASE(L)                                          \
+  case L: {                                                       \
+    constexpr int NLO = dtt_threads(sizeof(T) == 8, L);           \
+    if (a.nt > NLO) launch_dtt2_typed<T, L, 2 * NLO>(a, s);       \
+    else launch_dtt2_typed<T, L, NLO>(a, s);                      \
+    return;                                                       \
+  }
     switch (a.ap.n) {
       FFTC_DTT_CASE(16)
       FFTC_DTT_CASE(32)

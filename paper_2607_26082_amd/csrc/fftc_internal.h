@@ -127,6 +127,13 @@ inline bool dtt_compiled(int n) {
   return n == 16 || n == 32 || n == 48 || n == 64 || n == 96 || n == 128 || n == 256;
 }
 
+// Threads per block of a compile-time-length pass: these or twice as many, whichever the binding times
+// as the faster.  In FP32 up to length 128 the smaller blocks (8 to 32 lines) leave fewer lanes to
+// the odd last line of an axis of n + 1 nodes and more blocks to balance: against 256 or 512 threads
+// the z pass of 128x96x48 takes 23 in place of 33 us, of 128^3 28 in place of 34; at 256 nodes the
+// y and x inverse passes take 102 and 245 us with 256 and 512 threads, 114 and 238 with 128.
+constexpr int dtt_threads(bool fp64, int n) { return fp64 || n <= 128 ? 128 : 256; }
+
 // LDS of a plane of the plane route: two FP64 buffers, rows an odd number of values apart (16 lanes
 // reading the same y of 16 rows meet distinct banks)
 __host__ __device__ inline int plane_stride(int Ny) { return Ny | 1; }
