@@ -18,6 +18,7 @@
 
 #include <algorithm>
 #include <string>
+#include <type_traits>
 
 #include "../../include/fftc_nn.h"
 #include "fftc_nn_internal.h"
@@ -335,19 +336,25 @@ __global__ __launch_bounds__(256) void k_line(LineArgs a) {
             for (int t = 0; t < 2; ++t) acc[t] = mfma32(cs, bh[t], acc[t]);
           }
           uint32_t Zo[4];
+          auto finish = [&](auto first) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            float v0 = acc[0][e], v1 = acc[1][e];
-            if constexpr (EPI == EPI_GELU_Z) Zo[e] = pack_bf(v0, v1);
-            if constexpr (EPI == EPI_GELU || EPI == EPI_GELU_Z) {
-              v0 = gelu(v0);
-              v1 = gelu(v1);
-            } else if constexpr (EPI == EPI_DGELU) {
-              v0 *= gelu_grad(bf2f((uint16_t)Z[h][e]));
-              v1 *= gelu_grad(bf2f((uint16_t)(Z[h][e] >> 16)));
+            for (int e = 0; e < decltype(first)::value; ++e) {
+              float v0 = acc[0][e], v1 = acc[1][e];
+              if constexpr (EPI == EPI_GELU_Z) Zo[e] = pack_bf(v0, v1);
+              if constexpr (EPI == EPI_GELU || EPI == EPI_GELU_Z) {
+                v0 = gelu(v0);
+                v1 = gelu(v1);
+              } else if constexpr (EPI == EPI_DGELU) {
+                v0 *= gelu_grad(bf2f((uint16_t)Z[h][e]));
+                v1 *= gelu_grad(bf2f((uint16_t)(Z[h][e] >> 16)));
+              }
+              P[h][e] = pack_bf(v0, v1);
             }
-            P[h][e] = pack_bf(v0, v1);
-          }
+          };
+          // a last tile of one node (a line of 2^k + 1) has it in the first element: the other three
+          // values a lane would take through the GELU are left out
+          if (x + 1 == Nx) finish(std::integral_constant<int, 1>{});
+          else finish(std::integral_constant<int, 4>{});
           // stores: unguarded on whole tiles (the guard is uniform there)
           const size_t nd = (size_t)(base + x + 4 * q);
           if (x + 16 <= Nx) {
