@@ -504,9 +504,133 @@ __device__ __forceinline__ void node_p(const Geo& g, const Bufs<T>& B, long long
   b = bcount(g, xyz);
 }
 
+// Part of voxel a (corner (ax, ay, az) = bits of a is the node) in component c of the force -F at
+// node (i, j, k): stress of its tetrahedron that holds the node, times the node's gradient; 0 outside
+template <typename T, bool FS>
+__device__ __forceinline__ double corner_force(const Geo& g, const Bufs<T>& B, int i, int j, int k, int a, int c) {
+  const int xyz[3] = {i, j, k}, ab[3] = {a & 1, (a >> 1) & 1, a >> 2};
+  int at[3][2];   // node coordinate of the voxel's corners along each axis
+  long long vid = 0;
+  bool inside = true;
+#pragma unroll
+  for (int J = 2; J >= 0; --J) {
+    int v = xyz[J] - ab[J];
+    if (g.periodic[J]) v = v < 0 ? v + g.n[J] : v;
+    else inside = inside && v >= 0 && v < g.n[J];
+    vid = vid * g.n[J] + v;
+    at[J][0] = v;
+    at[J][1] = g.periodic[J] && v + 1 == g.N[J] ? 0 : v + 1;
+  }
+  if (!inside) return 0.0;
+  const int par = (ab[0] + ab[1] + ab[2]) & 1;
+  const T l = B.lam[vid], m = B.mu[vid];
+  T u[4][3];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    // corners 000, 110, 101, 011, or those with x reversed
+    const int cx = ((t == 1 || t == 2) ? 1 : 0) ^ par, cy = t == 1 || t == 3, cz = t >= 2;
+    const long long nd = at[0][cx] + (long long)g.N[0] * (at[1][cy] + (long long)g.N[1] * at[2][cz]);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) u[t][r] = B.u[r * g.Nn + nd];
+  }
+  const T fx = par ? T(-0.5) : T(0.5);
+  T G[3][3], s[3][3];
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+    const T p = u[1][r] - u[0][r], q = u[2][r] - u[3][r];
+    G[r][0] = fx * (p + q);
+    G[r][1] = T(0.5) * (p - q);
+    G[r][2] = T(0.5) * ((u[2][r] - u[0][r]) + (u[3][r] - u[1][r]));
+  }
+  if constexpr (FS) {
+    svk_pk1<T>(G, l, m, s);
+  } else {
+    const T tr = l * (G[0][0] + G[1][1] + G[2][2]);
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) s[r][q] = m * (G[r][q] + G[q][r]) + (r == q ? tr : T(0));
+  }
+  const T b0 = ab[0] ? T(0.25) : T(-0.25), b1 = ab[1] ? T(0.25) : T(-0.25), b2 = ab[2] ? T(0.25) : T(-0.25);
+  T f[3];
+#pragma unroll
+  for (int r = 0; r < 3; ++r) f[r] = b0 * s[r][0] + b1 * s[r][1] + b2 * s[r][2];
+  return (double)(c == 0 ? f[0] : c == 1 ? f[1] : f[2]);
+}
+
+// k_weak (below) of TETRA2, eight lanes per support node, one for each voxel around it: 14 loads and one
+// stress a lane, where a lane that evaluates its node alone has 55 loads, eight stresses and the
+// stencil in a row (10.2 -> 4.4 us on the averages of a 30x22x26 cell, all of it latency).
+template <typename T, bool FS>
+__global__ __launch_bounds__(kBlock) void k_weak_t(Geo g, Bufs<T> B, WeakDev w, DevState* st, int force) {
+  if (!force && st->done) return;
+  const long long r = (blockIdx.x * (long long)blockDim.x + threadIdx.x) >> 6;
+  if (r >= w.m) return;   // uniform over the wavefront
+  const int lane = threadIdx.x & 63, a = lane & 7;
+  const long long o0 = w.off[r];
+  const int cnt = (int)(w.off[r + 1] - o0), c = w.comp[r];
+  constexpr int R = 8;   // rounds of eight nodes: at most 64 support nodes
+  double qv[R], wa[R], wb[R];
+  int nd[R], bc[R];
+#pragma unroll
+  for (int t = 0; t < R; ++t) {
+    const int o = 8 * t + (lane >> 3);
+    const bool act = o < cnt;
+    nd[t] = act ? (int)w.nodes[o0 + o] : -1;
+    wa[t] = act ? w.wa[o0 + o] : 0.0;
+    wb[t] = act ? w.wb[o0 + o] : 0.0;
+    if (8 * (t + 1) >= cnt) break;   // uniform
+  }
+  double num = 0.0, den = 0.0, sb = 0.0;
+#pragma unroll
+  for (int t = 0; t < R; ++t) {
+    double f = 0.0;
+    bc[t] = 0;
+    bool anti = false;
+    if (nd[t] >= 0) {
+      const int y = nd[t] / g.N[0], k = y / g.N[1];
+      const int xyz[3] = {nd[t] - y * g.N[0], y - k * g.N[1], k};
+      f = corner_force<T, FS>(g, B, xyz[0], xyz[1], xyz[2], a, c);
+      bc[t] = bcount(g, xyz);
+      anti = is_antisym(g, c, xyz);
+    }
+    f += dpp_move<0xb1>(f);    // lane xor 1
+    f += dpp_move<0x4e>(f);    // lane xor 2
+    f += dpp_move<0x141>(f);   // mirrored in halves of a row
+    qv[t] = anti ? 0.0 : -f;
+    if (a == 0) {
+      num += wa[t] * qv[t];
+      den += wa[t] * wb[t];
+      sb += wb[t];
+    }
+    if (8 * (t + 1) >= cnt) break;   // uniform
+  }
+  num = wave_sum(num);
+  den = wave_sum(den);
+  sb = wave_sum(sb);
+  const double f = num / den;
+  double pn = 0.0;
+  T* const X = p_field(B, st) + c * g.Nn;
+#pragma unroll
+  for (int t = 0; t < R; ++t) {
+    if (nd[t] >= 0 && a == 0) {
+      const double scale = (double)(1 << bc[t]), pnew = (qv[t] - wb[t] * f) * scale;
+      pn += pnew * pnew;
+      X[nd[t]] = (T)((double)X[nd[t]] - wb[t] * f * scale);
+    }
+    if (8 * (t + 1) >= cnt) break;   // uniform
+  }
+  pn = wave_sum(pn);
+  if (lane == 0) {
+    w.part[r] = pn;
+    w.react[r] = -f * sb;
+  }
+}
+
 // proj_P of the relations on several nodes on the physical residual q = 2^-b p (eq 14,
 // eq 17): f = (wa . q) / (wa . wb), q -= wb f over the support.  One wavefront per relation,
-// one lane per support node; the residual of every support node is formed again from u.
+// one lane per support node; the residual of every support node is formed again from u.  HEX1
+// (TETRA2 runs k_weak_t).
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_weak(Geo g, Bufs<T> B, WeakDev w, DevState* st, int force) {
   if (!force && st->done) return;
@@ -1284,7 +1408,10 @@ int launch_residual(const Geo& g, const Bufs<T>& B, const ContactDev& ct, DevSta
 template <typename T>
 void launch_weak(const Geo& g, const Bufs<T>& B, const WeakDev& w, DevState* st, int force, hipStream_t s) {
   if (w.m == 0) return;
-  hipLaunchKernelGGL(k_weak<T>, dim3(rel_grid(w.m)), dim3(kBlock), 0, s, g, B, w, st, force);
+  const dim3 grid(rel_grid(w.m)), block(kBlock);
+  if (g.hex) hipLaunchKernelGGL(k_weak<T>, grid, block, 0, s, g, B, w, st, force);
+  else if (g.fs) hipLaunchKernelGGL((k_weak_t<T, true>), grid, block, 0, s, g, B, w, st, force);
+  else hipLaunchKernelGGL((k_weak_t<T, false>), grid, block, 0, s, g, B, w, st, force);
 }
 
 void launch_control(DevState* st, const double* part, int nblk, const double* wpart, long long nweak,

@@ -106,3 +106,32 @@ def test_accelerated_iterates(nx, period):
     g.solve()
     u = g.u.cpu().numpy().reshape(o["u"].shape)
     assert np.linalg.norm(u - o["u"]) <= 1e-9 * np.linalg.norm(o["u"])
+
+
+@pytest.mark.parametrize("size", [2, 7, 8, 9, 40, 63, 64])
+@pytest.mark.parametrize("per", [None, 0, 2])
+@pytest.mark.parametrize("fs", [False, True])
+def test_projection_on_supports(size, per, fs):
+    """proj_P of averages whose support fills part of a round of eight nodes, whole rounds and all
+    eight rounds, on nodes anywhere in the grid (faces, edges, the seam of a periodic axis), against
+    the oracle.  FP64 rounding: 1e-12."""
+    F = _lib()
+    n = (9, 8, 7)
+    print(f"[supports] size={size} periodic={per} finite_strain={fs}", flush=True)
+    rng = np.random.default_rng(1700 + size)
+    lam = rng.uniform(0.4, 2.5, n[::-1]); mu = rng.uniform(0.3, 1.8, n[::-1])
+    bc = np.zeros((3, 3, 2), np.int8)
+    if per is not None:
+        bc[:, per, :] = W.BC_P
+    N = [n[J] + (J != per) for J in range(3)]
+    at = rng.permutation(N[0] * N[1] * N[2])[:3 * size].reshape(3, size)
+    sup = np.stack([at % N[0], at // N[0] % N[1], at // (N[0] * N[1])], -1)
+    avg = [W.Average(sup, np.array([0, 1, 2], np.int8), np.array([0.01, -0.02, 0.015]), set_id=0)]
+    o = OSolver(n, lam, mu, bc, (), avg, r0_factor=1.3, finite_strain=fs)
+    g = F.Solver(n, lam, mu, bc, (), avg, r0_factor=1.3, precision="fp64", finite_strain=fs)
+    u = rng.standard_normal(o.zeros().shape) * 2e-2
+    parts = o.iterate_parts(u)
+    p, pt, sums = g.stage_residual(u)
+    assert np.abs(pt - parts["ptil"]).max() <= 1e-12 * np.abs(parts["ptil"]).max()
+    assert np.abs(p - parts["p"]).max() <= 1e-12 * np.abs(parts["p"]).max()
+    assert abs(sums[0] - parts["pnorm2"]) <= 1e-11 * parts["pnorm2"]
