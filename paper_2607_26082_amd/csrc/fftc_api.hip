@@ -594,10 +594,7 @@ int launches_of(const fftc_problem* h, int it, bool fine) {
     }
   }
   // without contact the Anderson index is the iteration
-  if (!h->has_sphere && h->cfg.acv == FFTC_ACV_P) {
-    if (it < 1) w &= ~L_STORE;
-    if (it < 4 || it % h->cfg.period != 0) w &= ~L_ACCEL;
-  }
+  if (!h->has_sphere && h->cfg.acv == FFTC_ACV_P && (it < 4 || it % h->cfg.period != 0)) w &= ~L_ACCEL;
   return w;
 }
 

@@ -59,7 +59,6 @@ struct Geo {
 struct DevState {
   int done, status, it, i_local;
   int store_r, accel, accel_ok, acv;
-  int prev_ok, pad0;   // accel_ok of the iteration before (ring: where its input is)
   int have_prev, updates, restarts, vpar;
   int period, max_iter, contact, nC;
   int vnonempty, fine, inc_k, best_it;  // fine: the FP32 form forms stresses in FP64 (sticky);
@@ -82,7 +81,7 @@ constexpr unsigned kProgressDone = 1u << 31, kProgressFine = 1u << 30, kProgress
 
 // Kernels of one iteration that the device state may select; the host leaves out the ones it
 // knows cannot be.
-enum { L_U = 1, L_INC = 2, L_U64 = 4, L_STORE = 8, L_ACCEL = 16, L_ALL = 31 };
+enum { L_U = 1, L_INC = 2, L_U64 = 4, L_ACCEL = 8, L_ALL = 15 };
 
 enum StatusCode { ST_RUNNING = 0, ST_CONVERGED = 1, ST_NOCONV = 2, ST_NAN = 3 };
 
@@ -162,7 +161,7 @@ struct Bufs {
   // ACV_P (ring): the residual pass of iteration it writes p~ into S[it mod 4] and S_i is that field,
   // or X after an accelerating iteration; R_i + S_i is then p~_{i+1}, so that the accelerated
   // combination reads four fields in place of eight, and a plain iteration stores no input.
-  // R_i is in slot it mod 4 of its iteration.
+  // R_i is in slot it mod 4 of its iteration, written by the next one's residual pass.
   int ring;
   const T* lam;
   const T* mu;

@@ -6,7 +6,8 @@
 //                DOFs and contact nodes, reference-medium term, FP64 partial norms
 //   k_weak       proj_P of the relations on several nodes (eq 14, eq 17)
 //   k_control    equilibrium test (eq 5), contact active-set update, Anderson flags
-//   k_anderson_r / k_alpha   residual store, FP64 Gram matrix, constrained LS
+//   k_gram4 / k_alpha   FP64 Gram matrix of the stored residuals, constrained LS (k_anderson_r:
+//                the store and the matrix of the form accelerated on u)
 //   (the per-axis DTT passes, Tables 2-3, are in fftc_dtt_kernels.h; the residual-form
 //    iteration of the FP32 path is in fftc_residual.hip)
 //   k_proj_*     proj_U: relations (eq 11, eq 15), contact radial projection, strong DOFs
@@ -249,18 +250,28 @@ __device__ __forceinline__ void node_eval_any(const Geo& g, const T* __restrict_
 // ---------------------------------------------------------------------------
 // Residual pass
 // ---------------------------------------------------------------------------
-// field of p~ of the current iteration
+// Where the pass of an iteration leaves p~, and (ring, past the first iteration of a history) the
+// residual R = p~ - S of the iteration before: accel_ok is still that iteration's
 template <typename T>
-__device__ __forceinline__ T* p_field(const Bufs<T>& B, const DevState* st) {
-  return B.ring ? B.S[st->it & 3] : B.X;
+struct ResOut {
+  T* X;
+  T* R;         // null: not formed
+  const T* S;
+};
+template <typename T>
+__device__ __forceinline__ ResOut<T> res_out(const Bufs<T>& B, const DevState* st) {
+  if (!B.ring) return ResOut<T>{B.X, nullptr, nullptr};
+  const int it = st->it;
+  const bool r = st->i_local > 0;
+  return ResOut<T>{B.S[it & 3], r ? B.R[(it + 3) & 3] : nullptr, st->accel_ok ? B.X : B.S[(it + 3) & 3]};
 }
 
 // proj_P of the strong conditions and the obstacle at one node of mask m, its part of |p|^2 into pn2,
-// and p (write_p) or p + K0 u into X
+// and p (write_p) or p + K0 u into X (and R from sp, the value of S)
 template <typename T>
 __device__ __forceinline__ void residual_tail(const Geo& g, const Bufs<T>& B, const ContactDev& ct, int cur, int i, int j,
                                               int k, long long node, uint8_t m, T p[3], const T k0[3], int write_p,
-                                              T* X, double& pn2) {
+                                              const ResOut<T>& o, const T sp[3], double& pn2) {
   const long long Nn = g.Nn;
   if (ct.on && (m & M_FACE)) {
     const int xyz[3] = {i, j, k};
@@ -291,7 +302,11 @@ __device__ __forceinline__ void residual_tail(const Geo& g, const Bufs<T>& B, co
     }
   }
 #pragma unroll
-  for (int c = 0; c < 3; ++c) X[c * Nn + node] = write_p ? p[c] : p[c] + k0[c];
+  for (int c = 0; c < 3; ++c) {
+    const T v = write_p ? p[c] : p[c] + k0[c];
+    o.X[c * Nn + node] = v;
+    if (o.R) o.R[c * Nn + node] = v - sp[c];
+  }
 }
 
 // One node per thread, its neighbours through the caches: HEX1, and node planes wider than
@@ -307,7 +322,7 @@ __global__ __launch_bounds__(kBlock) void k_residual(Geo g, Bufs<T> B, ContactDe
   const int Nx = g.N[0], Ny = g.N[1];
   const long long Nn = g.Nn;
   const int cur = ct.on ? st->vpar : 0;
-  T* const X = p_field(B, st);
+  const ResOut<T> out = res_out(B, st);
   long long lo, hi;
   xcd_chunk(Nn, lo, hi);
   for (long long node = lo + threadIdx.x; node < hi; node += blockDim.x) {
@@ -322,7 +337,11 @@ __global__ __launch_bounds__(kBlock) void k_residual(Geo g, Bufs<T> B, ContactDe
     acc[1] += sn;
 #pragma unroll
     for (int q = 0; q < 6; ++q) acc[2 + q] += ms[q];
-    residual_tail<T>(g, B, ct, cur, i, j, k, node, B.mask[node], p, k0, write_p, X, acc[0]);
+    T sp[3] = {T(0), T(0), T(0)};
+    if (out.R)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) sp[c] = out.S[c * Nn + node];
+    residual_tail<T>(g, B, ct, cur, i, j, k, node, B.mask[node], p, k0, write_p, out, sp, acc[0]);
   }
   block_sum<kPartStride>(acc, sh);
   if (threadIdx.x == 0)
@@ -334,7 +353,7 @@ __global__ __launch_bounds__(kBlock) void k_residual(Geo g, Bufs<T> B, ContactDe
 // Kz = A_z + S_{z-1} and S_z, where A = st0 u + st1 (in-plane diagonal neighbours) and S = st2 (x
 // neighbours) + st3 (y neighbours) of a plane, so that a plane is read from LDS once.
 // Bound by the latency of a step at two blocks per CU (182 VGPRs, 59 KB of LDS), then by FP64
-// issue: at 128^3 76 us for 137 MB (157 us with one node per thread, every node forming its 24
+// issue: at 128^3 76 us for 137 MB, R not formed (157 us with one node per thread, every node forming its 24
 // corner forces from 39 values of u out of the caches), at 64^3 26 us (49), at 16^3 14 us (20).
 template <typename T, bool FS>
 __global__ __launch_bounds__(256) void k_residual_t(Geo g, Bufs<T> B, ContactDev ct, DevState* st,
@@ -353,7 +372,7 @@ __global__ __launch_bounds__(256) void k_residual_t(Geo g, Bufs<T> B, ContactDev
   const int Nx = g.N[0], Ny = g.N[1], Nz = g.N[2], NxNy = Nx * Ny;
   const int zb = bz * tg.seg, ze = min(zb + tg.seg, Nz);
   const int cur = ct.on ? st->vpar : 0;
-  T* const X = p_field(B, st);
+  const ResOut<T> out = res_out(B, st);
   int off[kPR];
   plane_offsets(g, x0, y0, tid, off);
   T rd[kPR];
@@ -432,6 +451,10 @@ __global__ __launch_bounds__(256) void k_residual_t(Geo g, Bufs<T> B, ContactDev
   for (int z = zb; z < ze; ++z) {
     const long long node = (long long)i + (long long)Nx * j + (long long)NxNy * z;
     const uint8_t m = nact ? B.mask[node] : 0;
+    T sp[3] = {T(0), T(0), T(0)};
+    if (nact && out.R)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) sp[c] = out.S[c * g.Nn + node];
     T (*ex)[kVY][kVX] = sx[z & 1];
     T F0[3];   // forces on the thread's own corner (0, 0)
     {
@@ -476,7 +499,7 @@ __global__ __launch_bounds__(256) void k_residual_t(Geo g, Bufs<T> B, ContactDev
         p[c] = a ? T(0) : -w2b * F;
         k0[c] = a ? T(0) : Kz[c] + S1[c];
       }
-      residual_tail<T>(g, B, ct, cur, i, j, z, node, m, p, k0, write_p, X, acc[0]);
+      residual_tail<T>(g, B, ct, cur, i, j, z, node, m, p, k0, write_p, out, sp, acc[0]);
     }
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -610,13 +633,16 @@ __global__ __launch_bounds__(kBlock) void k_weak_t(Geo g, Bufs<T> B, WeakDev w, 
   sb = wave_sum(sb);
   const double f = num / den;
   double pn = 0.0;
-  T* const X = p_field(B, st) + c * g.Nn;
+  const ResOut<T> out = res_out(B, st);
 #pragma unroll
   for (int t = 0; t < R; ++t) {
     if (nd[t] >= 0 && a == 0) {
       const double scale = (double)(1 << bc[t]), pnew = (qv[t] - wb[t] * f) * scale;
       pn += pnew * pnew;
-      X[nd[t]] = (T)((double)X[nd[t]] - wb[t] * f * scale);
+      const long long e = c * g.Nn + nd[t];
+      const T v = (T)((double)out.X[e] - wb[t] * f * scale);
+      out.X[e] = v;
+      if (out.R) out.R[e] = v - out.S[e];
     }
     if (8 * (t + 1) >= cnt) break;   // uniform
   }
@@ -657,8 +683,11 @@ __global__ __launch_bounds__(kBlock) void k_weak(Geo g, Bufs<T> B, WeakDev w, De
   const double pnew = (q - wb * f) * scale;
   const double pn = wave_sum(act ? pnew * pnew : 0.0);
   if (act) {
-    T* X = p_field(B, st) + c * g.Nn + node;
-    *X = (T)((double)*X - wb * f * scale);
+    const ResOut<T> out = res_out(B, st);
+    const long long e = c * g.Nn + node;
+    const T v = (T)((double)out.X[e] - wb * f * scale);
+    out.X[e] = v;
+    if (out.R) out.R[e] = v - out.S[e];
   }
   if (lane == 0) {
     w.part[r] = pn;
@@ -859,13 +888,52 @@ __global__ __launch_bounds__(kCtlBlock) void k_control(DevState* st, const doubl
   if (threadIdx.x == 0) {
     st->store_r = (acv == 2) && (i_local > 0);
     st->accel = (acv == 2) && (i_local >= 4) && (i_local % period == 0);
-    st->prev_ok = st->accel_ok;
     st->accel_ok = 0;
   }
 }
 
 // ---------------------------------------------------------------------------
-// Anderson: R_{i-1 mod 4} = p~ - S_{i-1 mod 4}; Gram partials when accelerating
+// Anderson, ring: Gram matrix of the four residual fields, which the residual passes left
+// ---------------------------------------------------------------------------
+// Bound by the bytes, on small grids by the block sums: two values of every field per load.  (A pass
+// that formed R first read p~ and S again, 26 us at 128^3 in every plain iteration and 5 us at
+// 16^3; the residual pass, which has p~ at hand, spends 15 and less than 1.)
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_gram4(Bufs<T> B, long long n3, DevState* st, double* __restrict__ gpart) {
+  __shared__ double sh[10 * 16];
+  if (st->done || !st->accel) return;
+  double acc[10];
+#pragma unroll
+  for (int q = 0; q < 10; ++q) acc[q] = 0.0;
+  auto add = [&](const double (&r)[4]) {
+    int t = 0;
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = a; b < 4; ++b) acc[t++] += r[a] * r[b];
+  };
+  typedef T T2 __attribute__((ext_vector_type(2)));
+  const long long n2 = n3 / 2, step = (long long)gridDim.x * blockDim.x;   // (fields are 256-byte aligned)
+  const long long t0 = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  for (long long e = t0; e < n2; e += step) {
+    T2 v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = ((const T2*)B.R[q])[e];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) add({(double)v[0][k], (double)v[1][k], (double)v[2][k], (double)v[3][k]});
+  }
+  if (t0 < n3 - 2 * n2) {
+    const long long e = 2 * n2 + t0;
+    add({(double)B.R[0][e], (double)B.R[1][e], (double)B.R[2][e], (double)B.R[3][e]});
+  }
+  block_sum<10>(acc, sh);
+  if (threadIdx.x == 0)
+#pragma unroll
+    for (int q = 0; q < 10; ++q) gpart[q * kPartRows + blockIdx.x] = acc[q];
+}
+
+// ---------------------------------------------------------------------------
+// Anderson on the displacement (ACV_U): R_{i-1 mod 4} = X - S_{i-1 mod 4}; Gram partials when accelerating
 // ---------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_anderson_r(Bufs<T> B, long long n3, DevState* st,
@@ -874,17 +942,16 @@ __global__ __launch_bounds__(kBlock) void k_anderson_r(Bufs<T> B, long long n3, 
   if (st->done) return;
   const int store = st->store_r, accel = st->accel;
   if (!store && !accel) return;
-  const int s = ((B.ring ? st->it : st->i_local) + 3) & 3;
+  const int s = (st->i_local + 3) & 3;
   double acc[10];
 #pragma unroll
   for (int q = 0; q < 10; ++q) acc[q] = 0.0;
   T* Rs = B.R[s];
-  const T* Ss = B.ring && st->prev_ok ? B.X : B.S[s];
-  const T* X = p_field(B, st);
+  const T* Ss = B.S[s];
   for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < n3; e += (long long)gridDim.x * blockDim.x) {
     T r[4];
     if (store) {
-      r[s] = X[e] - Ss[e];
+      r[s] = B.X[e] - Ss[e];
       Rs[e] = r[s];
     }
     if (accel) {
@@ -1421,9 +1488,14 @@ void launch_control(DevState* st, const double* part, int nblk, const double* wp
 
 template <typename T>
 void launch_anderson(const Bufs<T>& B, long long n3, DevState* st, double* gpart, int nblk, int which, hipStream_t s) {
-  if (which & (L_STORE | L_ACCEL))
+  if (B.ring) {
+    if (!(which & L_ACCEL)) return;
+    nblk = (int)std::max<long long>(1, std::min<long long>(nblk, n3 / (4 * kBlock)));
+    hipLaunchKernelGGL(k_gram4<T>, dim3(nblk), dim3(kBlock), 0, s, B, n3, st, gpart);
+  } else {
     hipLaunchKernelGGL(k_anderson_r<T>, dim3(nblk), dim3(kBlock), 0, s, B, n3, st, gpart);
-  if (which & L_ACCEL) hipLaunchKernelGGL(k_alpha, dim3(1), dim3(kBlock), 0, s, st, gpart, nblk);
+  }
+  hipLaunchKernelGGL(k_alpha, dim3(1), dim3(kBlock), 0, s, st, gpart, nblk);
 }
 
 template <typename T>
