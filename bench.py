@@ -43,9 +43,9 @@ def stage_bytes(N, nv, precision):
         }
     f = 3 * N * 8
     return {
-        "residual": 2 * f + 2 * nv * 8,        # read u, lam, mu; write p~
-        "anderson": 3 * f + 4 * f / 2,         # read p~, S_prev; write R; read 4 R (accelerating)
-        "dtt_x_fwd": (8 * f + f) / 2 + 2 * f,  # read 4 S + 4 R (accelerating) or p~; write S, t
+        "residual": 4 * f + 2 * nv * 8,        # read u, S_prev, lam, mu; write p~, R
+        "anderson": 4 * f / 2,                 # read 4 R (accelerating)
+        "dtt_x_fwd": (5 * f + f) / 2 + f,      # read 4 p~ and write S (accelerating), or read p~; write t
         "dtt_y_fwd": 2 * f, "dtt_z_green": 2 * f, "dtt_y_inv": 2 * f, "dtt_x_inv": 2 * f,
     }
 
@@ -70,7 +70,7 @@ def b_alg_per_voxel_iter(N, nv, s, m=4, q=2):
 
 def kernel_source_digest():
     h = hashlib.sha256()
-    for f in ("fftc_residual.hip", "fftc_common.h", "fftc_internal.h"):
+    for f in ("fftc_residual.hip", "fftc_march.h", "fftc_common.h", "fftc_internal.h"):
         with open(os.path.join(ROOT, "paper_2607_26082_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()

@@ -1,5 +1,6 @@
-// Per-axis transforms as matrix products on the FP64 matrix cores, for the axis lengths that
-// have no compile-time FFT (fftc_dtt_kernels.h) and for periodic axes.
+// Transforms as matrix products on the FP64 matrix cores: per axis for the lengths that have no
+// compile-time FFT (fftc_dtt_kernels.h) and the short ones of small grids, and on small grids of
+// whole (y, z) planes (k_plane).
 //
 // Every transform of Table 2, and the half-complex DFT of a periodic axis, is a fixed N x N matrix
 // applied to the lines of the axis; k_dense_mats writes it once per binding in the order the

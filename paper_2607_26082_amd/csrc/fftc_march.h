@@ -8,8 +8,9 @@
 // eight corners, adds the forces on its lower corners to what the layer below left on them, and
 // passes three of the four corners' sums to its neighbours through LDS.  Against passing the
 // stresses (12 written and 48 read per thread and step, every corner force formed by the node)
-// this exchanges 9 values, forms each force once, and needs one barrier per step: planes and
-// exchange are double buffers, each rewritten only after the barrier that follows its last read.
+// this exchanges 9 values, forms each force once, and needs one barrier per step: planes are rings
+// of two or three, the exchange a double buffer, each rewritten only after the barrier that
+// follows its last read.
 #pragma once
 
 #include <atomic>
