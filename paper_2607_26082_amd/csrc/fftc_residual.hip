@@ -316,18 +316,25 @@ __global__ __launch_bounds__(kBlock) void k_residual_d(Geo g, DeltaBufs<T> D, Co
 // Registers set the blocks per CU: held to four, the incremental pass spills 6 of them and takes
 // 70 us at 128^3; at three nothing spills, which the passes with T stresses are held to as well
 // (those with contact or singular modes would spill).
-template <typename T, bool FS, bool GEN, typename TS, bool INC = false>
-__global__ __launch_bounds__(256)
-__attribute__((amdgpu_waves_per_eu(!GEN && sizeof(TS) == 4 ? 3 : 1)))
-void k_residual_dt(Geo g, DeltaBufs<T> D, ContactDev ct, DevState* st, double* __restrict__ part, TileGrid tg) {
+template <typename T, bool GEN, typename TS, bool INC>
+struct MarchLds {
+  static constexpr int NS = GEN ? kPartStrideD : 2;   // partial sums (INC leaves the second 0)
+  double su[INC ? 1 : 2][INC ? 1 : 3][INC ? 1 : kHY][INC ? 1 : kHX];
+  double sh[NS * 16];
+  TS sx[2][9][kVY][kVX];   // exchanged corner forces
+  T sdl[3][3][kHY][kHX];   // three planes: read in both halves of a step
+};
+template <typename T, bool FS, bool GEN, typename TS, bool INC>
+__device__ __forceinline__ void residual_march(const Geo& g, const DeltaBufs<T>& D, const ContactDev& ct,
+                                               const DevState* st, double* __restrict__ part, const TileGrid& tg,
+                                               MarchLds<T, GEN, TS, INC>& lds) {
   static_assert(!INC || (!FS && !GEN && sizeof(TS) == sizeof(T)), "incremental pass: small strain, T stresses");
   using TU = std::conditional_t<INC, T, double>;
-  constexpr int NS = GEN ? kPartStrideD : 2;   // partial sums (INC leaves the second 0)
-  __shared__ double su[INC ? 1 : 2][INC ? 1 : 3][INC ? 1 : kHY][INC ? 1 : kHX];
-  __shared__ T sdl[3][3][kHY][kHX];   // three planes: read in both halves of a step
-  __shared__ TS sx[2][9][kVY][kVX];   // exchanged corner forces
-  __shared__ double sh[NS * 16];
-  if (st->done || res_pass(st) != (INC ? PASS_INC : (sizeof(TS) == 8 ? PASS_U64 : PASS_U))) return;
+  constexpr int NS = MarchLds<T, GEN, TS, INC>::NS;
+  auto &su = lds.su;
+  auto &sdl = lds.sdl;
+  auto &sx = lds.sx;
+  double* const sh = lds.sh;
   const int tid = threadIdx.x;
   const int b = xcd_tile(blockIdx.x, gridDim.x);
   const int bx = b % tg.tx, by = (b / tg.tx) % tg.ty, bz = b / (tg.tx * tg.ty);
@@ -513,6 +520,31 @@ void k_residual_dt(Geo g, DeltaBufs<T> D, ContactDev ct, DevState* st, double* _
   if (blockIdx.x == 0)
     for (int q = 0; q < NS; ++q)
       for (int r = (int)gridDim.x + tid; r < tg.rows; r += 256) part[q * kPartRows + r] = 0.0;
+}
+
+template <typename T, bool FS, bool GEN, typename TS, bool INC = false>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(!GEN && sizeof(TS) == 4 ? 3 : 1)))
+void k_residual_dt(Geo g, DeltaBufs<T> D, ContactDev ct, DevState* st, double* __restrict__ part, TileGrid tg) {
+  __shared__ MarchLds<T, GEN, TS, INC> lds;
+  if (st->done || res_pass(st) != (INC ? PASS_INC : (sizeof(TS) == 8 ? PASS_U64 : PASS_U))) return;
+  residual_march<T, FS, GEN, TS, INC>(g, D, ct, st, part, tg, lds);
+}
+
+// Contact or singular modes, in a solve that may switch to FP64 stresses: both passes in one launch
+// (both run at two waves a SIMD, so neither loses by it; the launch that returned at once took
+// 4.5 us of 87 an iteration on a 64x64x48 indentation).
+template <typename T, bool FS>
+__global__ __launch_bounds__(256) void k_residual_dg(Geo g, DeltaBufs<T> D, ContactDev ct, DevState* st,
+                                                     double* __restrict__ part, TileGrid tg) {
+  using L32 = MarchLds<T, true, T, false>;
+  using L64 = MarchLds<T, true, double, false>;
+  __shared__ __align__(16) unsigned char lds[sizeof(L64) > sizeof(L32) ? sizeof(L64) : sizeof(L32)];
+  if (st->done) return;
+  if (res_pass(st) == PASS_U64)
+    residual_march<T, FS, true, double, false>(g, D, ct, st, part, tg, *reinterpret_cast<L64*>(lds));
+  else
+    residual_march<T, FS, true, T, false>(g, D, ct, st, part, tg, *reinterpret_cast<L32*>(lds));
 }
 
 // Mean stress of the residual-form iterate, once, when the solve is reported: per voxel the
@@ -847,20 +879,23 @@ __global__ __launch_bounds__(kBlock) void k_reactions_d(Geo g, DeltaBufs<T> D, S
 // ---------------------------------------------------------------------------
 
 template <typename T, typename TS>
-int launch_delta_residual_ts(const Geo& g, const DeltaBufs<T>& D, const ContactDev& ct, DevState* st, double* part,
-                             int nblk, const TileGrid& tg, hipStream_t s) {
+void launch_delta_residual_ts(const Geo& g, const DeltaBufs<T>& D, const ContactDev& ct, DevState* st, double* part,
+                              int nblk, const TileGrid& tg, bool gen, hipStream_t s) {
   if (tg.tx > 0) {
-    nblk = tg.tx * tg.ty * tg.nseg;
-    const bool gen = ct.on || g.sing[0] || g.sing[1] || g.sing[2];
-    if (g.fs && gen) hipLaunchKernelGGL((k_residual_dt<T, true, true, TS>), dim3(nblk), dim3(256), 0, s, g, D, ct, st, part, tg);
-    else if (g.fs) hipLaunchKernelGGL((k_residual_dt<T, true, false, TS>), dim3(nblk), dim3(256), 0, s, g, D, ct, st, part, tg);
-    else if (gen) hipLaunchKernelGGL((k_residual_dt<T, false, true, TS>), dim3(nblk), dim3(256), 0, s, g, D, ct, st, part, tg);
-    else hipLaunchKernelGGL((k_residual_dt<T, false, false, TS>), dim3(nblk), dim3(256), 0, s, g, D, ct, st, part, tg);
+    const dim3 grid(tg.tx * tg.ty * tg.nseg), block(256);
+    if constexpr (sizeof(TS) == 4) {
+      if (gen) {
+        if (g.fs) hipLaunchKernelGGL((k_residual_dt<T, true, true, TS>), grid, block, 0, s, g, D, ct, st, part, tg);
+        else hipLaunchKernelGGL((k_residual_dt<T, false, true, TS>), grid, block, 0, s, g, D, ct, st, part, tg);
+        return;
+      }
+    }
+    if (g.fs) hipLaunchKernelGGL((k_residual_dt<T, true, false, TS>), grid, block, 0, s, g, D, ct, st, part, tg);
+    else hipLaunchKernelGGL((k_residual_dt<T, false, false, TS>), grid, block, 0, s, g, D, ct, st, part, tg);
   } else {
     if (g.fs) hipLaunchKernelGGL((k_residual_d<T, true, TS>), dim3(nblk), dim3(kBlock), 0, s, g, D, ct, st, part);
     else hipLaunchKernelGGL((k_residual_d<T, false, TS>), dim3(nblk), dim3(kBlock), 0, s, g, D, ct, st, part);
   }
-  return nblk;
 }
 
 // The pass with T stresses, (refine) the pass with FP64 stresses and (inc) the incremental
@@ -872,9 +907,8 @@ int launch_delta_residual(const Geo& g, const DeltaBufs<T>& D, const ContactDev&
                           int nblk, int refine, int inc, int which, hipStream_t s) {
   const bool gen = ct.on || g.sing[0] || g.sing[1] || g.sing[2];
   const bool use_inc = inc && !g.fs && !gen;
-  // each pass on the grid for its own resident count (the incremental one's taken only when
-  // its segments are long enough); the control sums the largest count of rows, and a pass on
-  // a smaller grid clears the rows beyond it
+  // each pass on the grid for its own resident count; the control sums the largest count of rows,
+  // and a pass on a smaller grid clears the rows beyond it
   TileGrid tf = residual_tiles(g, gen, false);
   TileGrid ti = use_inc ? residual_tiles(g, false, true) : tf;
   TileGrid tu = refine ? residual_tiles_fp64(g, gen) : tf;
@@ -882,8 +916,15 @@ int launch_delta_residual(const Geo& g, const DeltaBufs<T>& D, const ContactDev&
     const int rows = std::max(tf.rows, std::max(ti.rows, tu.rows));
     tf.rows = ti.rows = tu.rows = rows;
   }
-  if (which & L_U) launch_delta_residual_ts<T, T>(g, D, ct, st, part, nblk, tf, s);
-  if (refine && (which & L_U64)) launch_delta_residual_ts<T, double>(g, D, ct, st, part, nblk, tu, s);
+  if (gen && refine && tu.tx > 0) {
+    const dim3 grid(tu.tx * tu.ty * tu.nseg), block(256);
+    tu.rows = grid.x;
+    if (g.fs) hipLaunchKernelGGL((k_residual_dg<T, true>), grid, block, 0, s, g, D, ct, st, part, tu);
+    else hipLaunchKernelGGL((k_residual_dg<T, false>), grid, block, 0, s, g, D, ct, st, part, tu);
+    return tu.rows;
+  }
+  if (which & L_U) launch_delta_residual_ts<T, T>(g, D, ct, st, part, nblk, tf, gen, s);
+  if (refine && (which & L_U64)) launch_delta_residual_ts<T, double>(g, D, ct, st, part, nblk, tu, gen, s);
   if (use_inc && ti.tx > 0 && (which & L_INC))
     hipLaunchKernelGGL((k_residual_dt<T, false, false, T, true>), dim3(ti.tx * ti.ty * ti.nseg), dim3(256), 0, s, g, D,
                        ct, st, part, ti);
@@ -987,11 +1028,13 @@ TileGrid residual_tiles(const Geo& g, bool gen, bool inc) {
     return tile_grid_for(g, gen ? residual_resident<true, true, float, false>() : residual_resident<true, false, float, false>());
   return tile_grid_for(g, gen ? residual_resident<false, true, float, false>() : residual_resident<false, false, float, false>());
 }
-// the pass with FP64 stresses
+// the pass with FP64 stresses (gen: both passes in one launch)
 TileGrid residual_tiles_fp64(const Geo& g, bool gen) {
-  if (g.fs)
-    return tile_grid_for(g, gen ? residual_resident<true, true, double, false>() : residual_resident<true, false, double, false>());
-  return tile_grid_for(g, gen ? residual_resident<false, true, double, false>() : residual_resident<false, false, double, false>());
+  static std::atomic<int> cache[2][64] = {};
+  if (gen)
+    return tile_grid_for(g, g.fs ? resident_blocks((const void*)k_residual_dg<float, true>, cache[1])
+                                 : resident_blocks((const void*)k_residual_dg<float, false>, cache[0]));
+  return tile_grid_for(g, g.fs ? residual_resident<true, false, double, false>() : residual_resident<false, false, double, false>());
 }
 
 template <typename T>

@@ -135,3 +135,29 @@ def test_projection_on_supports(size, per, fs):
     assert np.abs(pt - parts["ptil"]).max() <= 1e-12 * np.abs(parts["ptil"]).max()
     assert np.abs(p - parts["p"]).max() <= 1e-12 * np.abs(parts["p"]).max()
     assert abs(sums[0] - parts["pnorm2"]) <= 1e-11 * parts["pnorm2"]
+
+
+@pytest.mark.parametrize("n", [(30, 6, 3), (32, 7, 2), (60, 2, 9), (63, 13, 33)])
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("fs", [False, True])
+def test_march_with_singular_modes(n, f64, fs):
+    """The instance for an obstacle or singular modes (here: no fixed face), whose passes with FP32
+    and with FP64 stresses are one launch: one step from random fields as above."""
+    F = _lib()
+    print(f"[march] n={n} free faces fp64_stress={f64} finite_strain={fs}", flush=True)
+    rng = np.random.default_rng(1800 + n[0])
+    lam = rng.uniform(0.4, 2.5, n[::-1]); mu = rng.uniform(0.3, 1.8, n[::-1])
+    bc = np.zeros((3, 3, 2), np.int8)
+    o = OSolver(n, lam, mu, bc, r0_factor=1.3, finite_strain=fs)
+    g = F.Solver(n, lam, mu, bc, r0_factor=1.3, precision="fp32", finite_strain=fs)
+    u, delta, e, p_prev, R_prev = (rng.standard_normal(o.zeros().shape) * sc for sc in (2e-2, 1e-3, 2e-2, 2e-2, 2e-2))
+    pe = o.iterate_parts(u)["p"]
+    k0d = -o.reference_term(tetra2.tet_gradients(delta, o.plan))
+    p, R, dR, dY, sums = g.stage_residual_form(u, delta, e, p_prev, R_prev, 3, fp64_stress=int(f64))
+    tol = 2e-6 if f64 else 2e-5
+    assert np.abs(p - pe).max() <= tol * np.abs(pe).max()
+    assert abs(sums[0] - np.sum(pe ** 2)) <= 10 * tol * np.sum(pe ** 2)
+    Re = pe + k0d - e
+    assert np.abs(R - Re).max() <= tol * np.abs(Re).max()
+    dYe = pe - p_prev + k0d
+    assert np.abs(dY - dYe).max() <= tol * np.abs(dYe).max()
