@@ -147,7 +147,16 @@ struct SlotSlab {
 std::mutex g_slot_mu;
 SlotSlab g_slabs[64] = {};
 
+// Allocating or freeing while any thread captures a stream in the global mode (the default of a
+// caller's graph) would end that capture; here neither concerns it.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 HostSlot* take_slot() {
+  const RelaxedCapture relaxed;
   std::lock_guard<std::mutex> lk(g_slot_mu);
   for (SlotSlab& b : g_slabs) {
     if (b.used == ~0ull) continue;
@@ -168,6 +177,7 @@ HostSlot* take_slot() {
 
 void give_slot(HostSlot* s) {
   if (!s) return;
+  const RelaxedCapture relaxed;
   std::lock_guard<std::mutex> lk(g_slot_mu);
   for (SlotSlab& b : g_slabs) {
     const ptrdiff_t d = b.base ? (char*)s - b.base : -1;
