@@ -138,7 +138,8 @@ int fail(fftc_problem* h, int code, const std::string& msg) {
 
 // Slots of pinned host memory, one per handle that has solved, returned when it is destroyed: up to
 // 64 slabs of 64 (a handle beyond them, or one whose slab cannot be had, solves without).  A slab
-// is freed with its last slot, except the first.
+// is freed with its last slot, except the first.  A slot in a handle's hands is idle between its
+// calls: no queued work writes it (see settle).
 constexpr size_t kSlotBytes = (sizeof(HostSlot) + 127) / 128 * 128;
 struct SlotSlab {
   char* base;
@@ -732,6 +733,7 @@ int profile_t(fftc_problem* h, int iters, double* ms, int nst) {
   hs.status = 0;
   hs.max_iter = hs.it + iters + 8;
   hs.tol = 0.0;
+  hs.progress = nullptr;   // no solve is waiting for it
   HIPCHK(h, hipMemcpyAsync(h->st, &hs, sizeof(DevState), hipMemcpyHostToDevice, s));
   int nmark = 0;
   for (int it = 0; it < iters; ++it) {
@@ -850,6 +852,14 @@ int finish_report(fftc_problem* h, const DevState& out, double force_c, int nC, 
 constexpr int kForceRows = 64;   // blocks of the contact force (pairs in chk, the report after them)
 static_assert(8 * 2 * kForceRows + sizeof(SolveOut) <= sizeof(double) * 3 * 1024, "report in the check buffer");
 
+// After a failed HIP call, queued work may still write the handle's host words.  It is waited for; a
+// handle whose stream cannot be waited for gives its slot up, and nobody gets that one again.
+void settle(fftc_problem* h) {
+  if (hipStreamSynchronize(h->stream) == hipSuccess) return;
+  (void)hipGetLastError();
+  h->slot = nullptr;
+}
+
 // After the iterations: reactions of the returned iterate, output displacement, report.
 int solve_finish(fftc_problem* h, double* u_dev, fftc_report* rep) {
   hipStream_t s = h->stream;
@@ -911,8 +921,7 @@ int solve_finish(fftc_problem* h, double* u_dev, fftc_report* rep) {
 // to run), and no more than two idle ones after the solve is over.
 constexpr int kAhead = 3;
 
-int solve_all(fftc_problem* h, double* u_dev, int zero_start, fftc_report* rep) {
-  if (!h->slot && h->static_dev < 0) h->slot = take_slot();   // (a static binding allocates nothing)
+int solve_run(fftc_problem* h, double* u_dev, int zero_start, fftc_report* rep) {
   unsigned* const word = h->slot ? &h->slot->progress : nullptr;
   if (word) __atomic_store_n(word, 0u, __ATOMIC_RELEASE);
   int rc = solve_init(h, u_dev, zero_start, word);
@@ -959,6 +968,13 @@ int solve_all(fftc_problem* h, double* u_dev, int zero_start, fftc_report* rep) 
     __builtin_ia32_pause();
   }
   return solve_finish(h, u_dev, rep);
+}
+
+int solve_all(fftc_problem* h, double* u_dev, int zero_start, fftc_report* rep) {
+  if (!h->slot && h->static_dev < 0) h->slot = take_slot();   // (a static binding allocates nothing)
+  const int rc = solve_run(h, u_dev, zero_start, rep);
+  if (rc == FFTC_E_HIP) settle(h);
+  return rc;
 }
 
 template <typename T>
@@ -1904,6 +1920,7 @@ int fftc_batch_solve(fftc_batch_h b, double* const* u_dev, int32_t zero_start, f
   for (int c = 0; c < n; ++c) {
     const int rc = solve_finish(b->cells[c], u_dev ? u_dev[c] : nullptr, reps ? &reps[c] : nullptr);
     if (rc == FFTC_E_HIP) {
+      settle(b->cells[c]);
       restore();
       return rc;
     }
