@@ -195,7 +195,9 @@ int fftc_set_kinematics(fftc_h h, int32_t kind);
  * unknown acv. */
 int fftc_set_solver(fftc_h h, const fftc_solver_cfg* cfg);
 
-/* Device workspace needed by the current set-up (grid, precision, constraints). */
+/* Device workspace needed by the current set-up (grid, precision, boundary table,
+ * constraints).  It includes transform matrices for some axis lengths; a workspace that holds
+ * all but them is accepted too, and those axes then run slower transforms. */
 int fftc_workspace_bytes(fftc_h h, size_t* bytes);
 
 /* Bind caller-owned device memory (256-byte aligned) and the HIP stream (hipStream_t,

@@ -1457,7 +1457,7 @@ int fftc_workspace_bytes(fftc_h h, size_t* bytes) {
 namespace {
 // Binds ws to h: carves the fields, uploads tables and constraints, and (tune) times the two
 // block sizes of every transform pass; without tuning every pass takes the larger block.
-int bind_impl(fftc_h h, void* ws, size_t bytes, void* stream, bool tune, bool mats = true) {
+int bind_impl(fftc_h h, void* ws, size_t bytes, void* stream, bool tune) {
   if (!h || !ws) return FFTC_E_ARG;
   if (h->scheme == FFTC_HEX1 && h->precision != FFTC_FP64)
     return fail(h, FFTC_E_UNSUPPORTED, "the HEX1 scheme runs in FP64 (its hourglass modes have no FP32 residual form)");
@@ -1467,8 +1467,10 @@ int bind_impl(fftc_h h, void* ws, size_t bytes, void* stream, bool tune, bool ma
     return fail(h, FFTC_E_UNSUPPORTED,
                 "the isotropic reference medium needs HEX1 and periodic axes or normal-mixed faces");
   if (((uintptr_t)ws) % kAlign) return fail(h, FFTC_E_WORKSPACE, "workspace must be 256-byte aligned");
-  const size_t need = carve(h, nullptr, mats);
-  if (bytes < need) return fail(h, FFTC_E_WORKSPACE, "workspace too small");
+  // without the transform matrices where they do not fit: sizes asked for before the boundary table
+  // was set may lack room for the types of its axes
+  const bool mats = bytes >= carve(h, nullptr);
+  if (bytes < carve(h, nullptr, mats)) return fail(h, FFTC_E_WORKSPACE, "workspace too small");
   // contact face nodes may not carry other constraints
   if (h->has_sphere) {
     const int a = h->face / 2;
@@ -1678,9 +1680,7 @@ int fftc_bind_workspace(fftc_h h, void* ws, size_t bytes, void* stream) {
 
 int fftc_bind_workspace_static(fftc_h h, void* stream) {
   if (!h) return FFTC_E_ARG;
-  // (without the transform matrices where they would not fit)
-  const bool mats = carve(h, nullptr) <= kStaticWsBytes;
-  const size_t need = carve(h, nullptr, mats);
+  const size_t need = carve(h, nullptr, false);   // (the transform matrices where there is room)
   if (need > kStaticWsBytes)
     return fail(h, FFTC_E_WORKSPACE, "problem needs " + std::to_string(need) + " bytes of workspace, the static "
                                      "workspace holds " + std::to_string(kStaticWsBytes));
@@ -1706,7 +1706,7 @@ int fftc_bind_workspace_static(fftc_h h, void* stream) {
     g_static_owner[dev] = h;
   }
   h->static_dev = dev;
-  const int rc = bind_impl(h, ptr, kStaticWsBytes, stream, false, mats);
+  const int rc = bind_impl(h, ptr, kStaticWsBytes, stream, false);
   if (rc != FFTC_OK) release_static(h);
   return rc;
 }

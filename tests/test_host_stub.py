@@ -110,3 +110,21 @@ for h in again + [hs[k] for k in range(128) if k % 3]:
     F.fftc_destroy(h)
 assert stub.stub_slabs() == 1
 """)
+
+
+@pytest.mark.parametrize("n", [(20, 22, 26), (16, 16, 16), (64, 50, 8)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_workspace_sized_before_the_boundary_table(stub, n, prec):
+    """The default table has one transform type an axis, this one three: the size asked for first is
+    accepted, and only a size without the fields is not."""
+    _run(stub, f"""
+n, prec = {n}, {prec}
+bc = np.zeros((3, 3, 2), np.int8)
+bc[0, :, 0] = 1; bc[1, :, :] = 1         # x, y, z axes: DCT3 or DST3, DST1 and DCT1
+h = F.fftc_create(n, prec); early = F.fftc_workspace_bytes(h); F.fftc_destroy(h)
+h, rc = handle(n, prec, bc, early); assert rc == 0
+assert F.fftc_workspace_bytes(h) > early
+assert solve(h) != F.FFTC_E_HIP
+N = [v + 1 for v in n]; fields = 3 * N[0] * N[1] * N[2] * (80 if prec == 0 else 64)
+assert handle(n, prec, bc, fields)[1] == F.FFTC_E_WORKSPACE
+""")
