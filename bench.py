@@ -262,8 +262,8 @@ def bench_batch(args):
     batching gain."""
     if args.cells > BATCH_CELLS_MAX:
         print(json.dumps({"error": f"--cells {args.cells}: batches above {BATCH_CELLS_MAX} cells are switched off; "
-                                   "the 64-cell batch left the GPU faulted once with a transform variant that has "
-                                   "since been removed, and it stays off the GPU until the cause is shown"}))
+                                   "the 64-cell batch left the GPU faulted once, with an earlier kernel for paired "
+                                   "DCT3/DST3 lines, and stays off the GPU until the cause is shown"}))
         sys.exit(3)
     import torch
     import paper_2607_26082_amd as F

@@ -290,8 +290,8 @@ int fftc_stage_residual_form(fftc_h h, const double* u_dev, const double* delta_
  * fftc_solve on each cell.  stream: hipStream_t on which the batch runs (cells' own
  * streams are restored afterwards).  The batch creates up to 16 internal streams (default
  * priority) and one pinned host array; it allocates no device memory.
- * Cells with a rigid obstacle (fftc_set_sphere) and FP64 cells are not batched: create
- * returns FFTC_E_UNSUPPORTED (solve them with fftc_solve).
+ * Cells with a rigid obstacle (fftc_set_sphere), FP64 cells and more than 4 cells are not
+ * batched: create returns FFTC_E_UNSUPPORTED (solve them with fftc_solve).
  * batch_solve: u_dev[c] as in fftc_solve (NULL array = zero start for all); reps[count].
  * Returns FFTC_OK if every cell converged, else the first failing status. */
 typedef struct fftc_batch* fftc_batch_h;

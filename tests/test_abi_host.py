@@ -184,3 +184,13 @@ def test_network_shape_limits():
     big = F.fftc_nn_workspace_bytes(nn, (65, 65, 65), 0)
     assert small < train and small < big
     F.fftc_nn_destroy(nn)
+
+
+def test_large_batches_are_refused():
+    """More than 4 cells: refused before anything else about them is looked at (nothing is solved)."""
+    hs = [F.fftc_create((8, 8, 8), F.FFTC_FP32) for _ in range(5)]
+    assert _code(F.fftc_batch_create, hs, 0) == F.FFTC_E_UNSUPPORTED
+    assert _code(F.fftc_batch_create, hs * 13, 0) == F.FFTC_E_UNSUPPORTED
+    assert _code(F.fftc_batch_create, hs[:4], 0) == F.FFTC_E_STATE          # not bound
+    for h in hs:
+        F.fftc_destroy(h)
