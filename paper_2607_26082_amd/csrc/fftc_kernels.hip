@@ -431,7 +431,8 @@ __global__ __launch_bounds__(256) void k_residual_t(Geo g, Bufs<T> B, ContactDev
   voxel_lame(g, vox, zb - 1, B.lam, B.mu, lam, mu);
   __syncthreads();
   {
-    T up[4][3], fl[4][3], vs = T(0), ms[6], A[3], S[3];
+    T up[4][3], fl[4][3], A[3], S[3];
+    double vs = 0.0, ms[6];
     read_corners(zb - 1, lo);
     read_corners(zb, up);
     read_stencil(zb - 1, lo, A, S);
@@ -459,13 +460,13 @@ __global__ __launch_bounds__(256) void k_residual_t(Geo g, Bufs<T> B, ContactDev
     T F0[3];   // forces on the thread's own corner (0, 0)
     {
       T up[4][3], fl[4][3], fn[4][3];
-      T vs = T(0), ms[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};
+      double vs = 0.0, ms[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};   // (in FP64 for FP32 fields too)
       read_corners(z + 1, up);
       voxel_forces<T, T, FS, true>(lo, up, lam, mu, fl, fn, vs, ms);
       if (own) {
-        acc[1] += 8.0 * (double)vs;   // (1/2) sigma : sigma
+        acc[1] += 8.0 * vs;   // (1/2) sigma : sigma
 #pragma unroll
-        for (int q = 0; q < 6; ++q) acc[2 + q] += 2.0 * (double)ms[q];
+        for (int q = 0; q < 6; ++q) acc[2 + q] += 2.0 * ms[q];
       }
 #pragma unroll
       for (int c = 0; c < 3; ++c) {

@@ -51,10 +51,10 @@ __device__ __forceinline__ void plane_offsets(const Geo& g, int x0, int y0, int 
 // tetrahedra are {000, 110, 101, 011} and {100, 010, 001, 111}: each corner belongs to one.  The
 // gradient's halves and the force's quarters are folded into the Lame values (exact); differences
 // are formed in TU and rounded once to TS.  vs gains the voxel's sum of sigma : sigma / 16, ms the
-// components xx, yy, zz, yz, xz, xy of sigma / 4 summed over the tetrahedra.
-template <typename TU, typename TS, bool FS, bool SIG>
+// components xx, yy, zz, yz, xz, xy of sigma / 4 summed over the tetrahedra, both in TA.
+template <typename TU, typename TS, bool FS, bool SIG, typename TA>
 __device__ __forceinline__ void voxel_forces(const TU (&lo)[4][3], const TU (&up)[4][3], TS l, TS m, TS (&fl)[4][3],
-                                             TS (&fu)[4][3], TS& vs, TS (&ms)[6]) {
+                                             TS (&fu)[4][3], TA& vs, TA (&ms)[6]) {
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     TS G[3][3];
@@ -90,13 +90,13 @@ __device__ __forceinline__ void voxel_forces(const TU (&lo)[4][3], const TU (&up
       for (int r = 0; r < 3; ++r)
 #pragma unroll
         for (int q = 0; q < 3; ++q)
-          if (FS || q >= r) vs += ((!FS && q > r) ? TS(2) : TS(1)) * (s[r][q] * s[r][q]);
-      ms[0] += s[0][0];
-      ms[1] += s[1][1];
-      ms[2] += s[2][2];
-      ms[3] += s[1][2];
-      ms[4] += s[0][2];
-      ms[5] += s[0][1];
+          if (FS || q >= r) vs += ((!FS && q > r) ? TA(2) : TA(1)) * ((TA)s[r][q] * (TA)s[r][q]);
+      ms[0] += (TA)s[0][0];
+      ms[1] += (TA)s[1][1];
+      ms[2] += (TA)s[2][2];
+      ms[3] += (TA)s[1][2];
+      ms[4] += (TA)s[0][2];
+      ms[5] += (TA)s[0][1];
     }
 #pragma unroll
     for (int r = 0; r < 3; ++r) {

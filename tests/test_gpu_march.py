@@ -161,3 +161,20 @@ def test_march_with_singular_modes(n, f64, fs):
     assert np.abs(R - Re).max() <= tol * np.abs(Re).max()
     dYe = pe - p_prev + k0d
     assert np.abs(dY - dYe).max() <= tol * np.abs(dYe).max()
+
+
+@pytest.mark.parametrize("e", [0, 80])
+@pytest.mark.parametrize("n", [(6, 5, 4), (40, 9, 7)])
+def test_fp32_literal_stress_norm_is_summed_in_fp64(n, e):
+    """The literal residual pass on FP32 fields: uniaxial strain whose stress, 2 mu a = 2049 2051 2^(e - 32), is an
+    FP32 number but its square is not (and for e = 80 exceeds FP32).  Its sum over the voxels is exact in
+    FP64 up to its additions, at most as many as voxels."""
+    F = _lib()
+    lam = np.zeros(n[::-1]); mu = np.full(n[::-1], 2049.0 * 2.0 ** (e - 11))
+    g = F.Solver(n, lam, mu, np.zeros((3, 3, 2), np.int8), precision="fp32", acv="U")
+    u = np.zeros((3, n[2] + 1, n[1] + 1, n[0] + 1))
+    u[0] = np.arange(n[0] + 1) * (2051.0 * 2.0 ** -22)
+    print(f"[march] literal FP32 stress norm n={n} e={e}", flush=True)
+    _, _, sums = g.stage_residual(u)
+    exact = lam.size * (2049.0 * 2051.0 * 2.0 ** (e - 32)) ** 2
+    assert abs(sums[1] - exact) <= lam.size * 2.0 ** -53 * exact
