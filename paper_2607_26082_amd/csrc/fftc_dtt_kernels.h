@@ -759,13 +759,15 @@ __global__ __launch_bounds__(NTH) void k_dtt2(DttArgs<T> a) {
 // z pass (forward, symbol, inverse) of DCT3 and DST3 lines, two lines per complex FFT
 // ---------------------------------------------------------------------------
 // Both transforms have real data on one side of their FFT: the forward one's result is real, the
-// inverse one's input is.  Lines p and p + P of the block therefore share an FFT as its real
+// inverse one's input is.  Lines 2 p and 2 p + 1 of the block therefore share an FFT as its real
 // and imaginary part, which halves the butterflies, and with k_dtt2's two FFTs of a line each this
-// pass was bound by them.  Position k of the forward result holds coefficient m(k) = 2 k, or
+// pass was bound by them.  Neighbours, because the rounding of one line reaches the other: their
+// symbols are alike (a rough mode beside the mean, whose symbol is up to 1e4 smaller, made the error
+// of such a field 94 units of roundoff at 16x16x128 in FP64, where it is 4).  Position k of the forward result holds coefficient m(k) = 2 k, or
 // 2 n - 1 - 2 k past the middle, and the inverse reads coefficient m(k) at position k: the symbol
 // is applied as the second FFT loads, and DST3's alternating signs cancel.
 // Against a line per FFT (the symbol through LDS): FP32 256^3 202 -> 113 us (407 MB: 3.6 TB/s), 128^3
-// 45 -> 34, 96^3 37 -> 20, 128x96x48 33 -> 16, 64^3 18 -> 12; FP64 128^3 70 -> 47, 64^3 20 -> 15.
+// 45 -> 27, 96^3 37 -> 19, 128x96x48 33 -> 15, 64^3 18 -> 11; FP64 128^3 70 -> 46, 64^3 20 -> 15.
 template <typename T, int NF, int NTH>
 __global__ __launch_bounds__(NTH) void k_dtt2z(DttArgs<T> a) {
   using S = DttShape<NF, NTH>;
@@ -800,7 +802,7 @@ __global__ __launch_bounds__(NTH) void k_dtt2z(DttArgs<T> a) {
   }
   __syncthreads();
   fft_ct<T, NF, +1, NT>(cb, CS, tw, [&](int p, int k) -> cplx<T> {
-    const T *x1 = rb + p * RS, *x2 = x1 + P * RS;
+    const T *x1 = rb + 2 * p * RS, *x2 = x1 + RS;
     const int ia = sine ? NF - k : k, ib = NF - ia;
     const T a1 = x1[ia], a2 = x2[ia], b1 = k ? x1[ib] : T(0), b2 = k ? x2[ib] : T(0);
     return cmul(cconj(tw[k]), cplx<T>{a1 + b2, a2 - b1});
@@ -820,7 +822,7 @@ __global__ __launch_bounds__(NTH) void k_dtt2z(DttArgs<T> a) {
     const int p = (int)tid / S::TL;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int x = min(x0 + p + h * P, Nx - 1);
+      const int x = min(x0 + 2 * p + h, Nx - 1);
       const T sx = tab[x], qx = tab[a.maxN + x];
       A[h] = T(4) * (a0 * sx * qy + a1 * sy * qx + e2 * sx * sy);
       B[h] = T(4) * (e0 * qx * sy + e1 * qy * sx + a2 * qx * qy);
@@ -841,20 +843,28 @@ __global__ __launch_bounds__(NTH) void k_dtt2z(DttArgs<T> a) {
     return {r[0], r[1]};
   });
   {
-    // transforms of the two lines from Z: (Z_k + conj Z_{n-k}) / 2 and (Z_k - conj Z_{n-k}) / 2i
-    const unsigned p = tid % P, k0 = tid / P;
-    const bool ok1 = (int)p < nl, ok2 = (int)(p + P) < nl;
-    const cplx<T>* Z = cb + p * CS;
-    constexpr int KL = NT / P;   // KL NL = NF
+    // transforms of the two lines from Z: (Z_k + conj Z_{n-k}) / 2 and (Z_k - conj Z_{n-k}) / 2i.  A
+    // thread has one line and takes nodes k and n - k at once (the same sums, twiddles t and -i conj t),
+    // k = 0 with n / 2, so that a row of lanes stores a row of lines.
+    const unsigned l = tid % LB;
+    const bool ok = (int)l < nl, odd = l & 1;
+    const cplx<T>* Z = cb + (l >> 1) * CS;
     const T w = T(0.5 / NF);
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-      const int k = (int)k0 + i * KL, m = sine ? NF - k : k;
-      const cplx<T> u = Z[cpad<NF>(k)], v = Z[cpad<NF>(k ? NF - k : 0)], t = tw[k];
-      const T o1 = (t.re * (u.re + v.re) - t.im * (u.im - v.im)) * w;
-      const T o2 = (t.re * (u.im + v.im) - t.im * (v.re - u.re)) * w;
-      if (ok1) f[p + (unsigned)m * es] = o1;
-      if (ok2) f[p + P + (unsigned)m * es] = o2;
+      const int j = (int)(tid / LB) + i * ML, k2 = j ? NF - j : NF / 2;   // ML NL = n / 2
+      const cplx<T> u = Z[cpad<NF>(j)], v = Z[cpad<NF>(k2)], t = tw[j];
+      const T s = odd ? u.im + v.im : u.re + v.re, d = odd ? v.re - u.re : u.im - v.im;
+      T o1 = (t.re * s - t.im * d) * w, o2 = -(t.im * s + t.re * d) * w;
+      if (j == 0) {
+        o1 = T(2) * w * (odd ? u.im : u.re);
+        o2 = T(2) * w * tw[NF / 2].re * (odd ? v.im : v.re);
+      }
+      const int m1 = sine ? NF - j : j, m2 = sine ? NF - k2 : k2;
+      if (ok) {
+        f[l + (unsigned)m1 * es] = o1;
+        f[l + (unsigned)m2 * es] = o2;
+      }
     }
     // the node held at 0
     if (tid < (unsigned)LB && (int)tid < nl) f[tid + (sine ? 0u : (unsigned)NF) * es] = T(0);
