@@ -281,15 +281,27 @@ struct Layout {
   }
 };
 
-// Axes whose transforms run as matrix products (fftc_dense.hip): up to 256 nodes, every length
+// Axes whose transforms run as matrix products (fftc_dense.hip): up to 256 nodes, the lengths
 // without a compile-time FFT (per iteration, products against the runtime-length FFT: 30x22x26
 // FP64 88 against 165 us, 75x140x18 FP32 139 against 256, 140^3 FP32 692 against 1672 and FP64 832
-// against 1244).  Of the compile-time lengths 16, 32 and 48 on grids of at most 160,000 nodes, where
+// against 1244, 250^3 FP32 3345 against 4555).
+// Not so FP64 lines of 190 voxels and more on x and z where their cost, which grows with the
+// square of the length, has met the FFT's: at lengths of the factors 2, 3 and 5 (x passes of
+// 250x64x64 139 against 120 us, the z pass of 128x128x250 403 against 330; x lines of large planes stay:
+// 250x216x216 0.91 of the FFT's time), and at every length below 2048 lines, too few to hide the products'
+// latency (x passes of 252x32x32 1.3).  Other lengths have radices 7, 11 or 13 in the FFT (252x64x64 138
+// against 154, 128x128x234 358 against 447); y lines stay (64x250x64 0.83), and FP32 (0.4 to 1.1).
+// Of the compile-time lengths 16, 32 and 48 on grids of at most 160,000 nodes, where
 // the passes are bound by their chain of barriers, in FP32 (at 64^3 167 against 162) and on
 // periodic axes (a y pass at 48^3 periodic 8.4 against 9.2 us in FP64; longer periodic lines the
 // other way: 64^3 12 against 10, 256x256x16 57 against 25, in FP32 57 against 17).
 bool dense_axis(const fftc_problem* h, int J) {
   if (h->N[J] > 256) return false;
+  if (h->precision == FFTC_FP64 && J != 1 && h->n[J] >= 190) {
+    const long long lines = h->Nn / h->N[J];
+    const bool small_radices = h->n[J] % 7 && h->n[J] % 11 && h->n[J] % 13;
+    if (lines < 2048 || (small_radices && (J == 2 || lines < 32768))) return false;
+  }
   return !dtt_compiled(h->n[J]) ||
          (h->n[J] <= 48 && h->Nn <= 160000 && (h->precision == FFTC_FP32 || h->periodic[J]));
 }

@@ -194,3 +194,23 @@ def test_large_batches_are_refused():
     assert _code(F.fftc_batch_create, hs[:4], 0) == F.FFTC_E_STATE          # not bound
     for h in hs:
         F.fftc_destroy(h)
+
+
+@pytest.mark.parametrize("n,prec,axis,dense", [
+    ((180, 64, 64), 0, 0, True), ((200, 64, 64), 0, 0, False), ((64, 200, 64), 0, 1, True), ((64, 64, 200), 0, 2, False),
+    ((252, 64, 64), 0, 0, True), ((64, 64, 252), 0, 2, True), ((252, 32, 32), 0, 0, False), ((32, 32, 234), 0, 2, False),
+    ((250, 216, 216), 0, 0, True), ((216, 216, 250), 0, 2, False), ((250, 64, 64), 1, 0, True), ((64, 64, 64), 0, 0, False)])
+def test_axes_taken_as_matrix_products(n, prec, axis, dense):
+    """Long FP64 lines on x and z keep the FFT where its radices are small or the lines few.  Seen by the
+    workspace: an axis that runs as products has a matrix pair for each transform type on it."""
+    sizes = []
+    for types in (1, 3):
+        bc = np.zeros((3, 3, 2), np.int8)
+        if types == 3:
+            bc[0, axis, 0] = 1                       # DST3 or DCT3, DST1 and DCT1
+            bc[1, axis, :] = 1
+        h = F.fftc_create(n, prec)
+        F.fftc_set_bc(h, bc)
+        sizes.append(F.fftc_workspace_bytes(h))
+        F.fftc_destroy(h)
+    assert (sizes[1] > sizes[0]) == dense
