@@ -934,27 +934,25 @@ void launch_dtt(const DttArgs<T>& a, int ept, hipStream_t s) {
     launch_dense<T>(a, s);
     return;
   }
-  if (!a.generic) {
-    // block size chosen by the host autotuner (a.nt, one of dtt_threads)
-#define FFTC_DTT_CASE(L)                                          \
-  case L: {                                                       \
-    constexpr int NLO = dtt_threads(sizeof(T) == 8, L);           \
-    if (a.nt > NLO) launch_dtt2_typed<T, L, 2 * NLO>(a, s);       \
-    else launch_dtt2_typed<T, L, NLO>(a, s);                      \
-    return;                                                       \
+  // block size chosen by the host autotuner (a.nt, one of dtt_threads)
+#define FFTC_DTT_CASE(L)                                        \
+  case L: {                                                     \
+    constexpr int NLO = dtt_threads(sizeof(T) == 8, L);         \
+    if (a.nt > NLO) launch_dtt2_typed<T, L, 2 * NLO>(a, s);     \
+    else launch_dtt2_typed<T, L, NLO>(a, s);                    \
+    return;                                                     \
   }
-    switch (a.ap.n) {
-      FFTC_DTT_CASE(16)
-      FFTC_DTT_CASE(32)
-      FFTC_DTT_CASE(48)
-      FFTC_DTT_CASE(64)
-      FFTC_DTT_CASE(96)
-      FFTC_DTT_CASE(128)
-      FFTC_DTT_CASE(256)
-      default: break;
-    }
+  switch (a.ap.n) {
+    FFTC_DTT_CASE(16)
+    FFTC_DTT_CASE(32)
+    FFTC_DTT_CASE(48)
+    FFTC_DTT_CASE(64)
+    FFTC_DTT_CASE(96)
+    FFTC_DTT_CASE(128)
+    FFTC_DTT_CASE(256)
+    default: break;
+  }
 #undef FFTC_DTT_CASE
-  }
   const int Nx = a.g.N[0], Ny = a.g.N[1], Nz = a.g.N[2];
   const long long nlines = a.axis == 0 ? (long long)Ny * Nz : a.axis == 1 ? (long long)Nx * Nz : (long long)Nx * Ny;
   const long long nb = (nlines + a.ap.L - 1) / a.ap.L;

@@ -225,7 +225,6 @@ struct DttArgs {
   int maxN;
   int inv_types[3];
   double thr[3];
-  int generic;                 // force the runtime-length kernel
   int nt;                      // threads per block of the compile-time-length kernel
   // Plane route (k_plane): the x forward pass leaves every component as [x][z][y] in the field below,
   // the x inverse pass reads it there.  0: not taken; 1: in tr; 2, 3: in the R slot that the

@@ -887,7 +887,6 @@ __global__ __launch_bounds__(kCtlBlock) void k_control(DevState* st, const doubl
     }
   }
   if (threadIdx.x == 0) {
-    st->store_r = (acv == 2) && (i_local > 0);
     st->accel = (acv == 2) && (i_local >= 4) && (i_local % period == 0);
     st->accel_ok = 0;
   }
