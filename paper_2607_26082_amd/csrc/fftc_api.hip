@@ -931,8 +931,8 @@ int solve_finish(fftc_problem* h, double* u_dev, fftc_report* rep) {
 }
 
 // Iterations in the queue ahead of the last equilibrium test the host has seen: enough that
-// the device never waits for the host (an iteration takes about 25 us to enqueue and 60 us or more
-// to run), and no more than two idle ones after the solve is over.
+// the device never waits for the host (an iteration takes at most about 25 us to enqueue, and 41 us or
+// more to run: 16^3 in FP64), and no more than two idle ones after the solve is over.
 constexpr int kAhead = 3;
 
 int solve_run(fftc_problem* h, double* u_dev, int zero_start, fftc_report* rep) {
@@ -1470,7 +1470,8 @@ int fftc_workspace_bytes(fftc_h h, size_t* bytes) {
 
 namespace {
 // Binds ws to h: carves the fields, uploads tables and constraints, and (tune) times the two
-// block sizes of every transform pass; without tuning every pass takes the larger block.
+// block sizes of every transform pass; without tuning every pass takes the smaller, at 256 nodes the
+// larger.
 int bind_impl(fftc_h h, void* ws, size_t bytes, void* stream, bool tune) {
   if (!h || !ws) return FFTC_E_ARG;
   if (h->scheme == FFTC_HEX1 && h->precision != FFTC_FP64)

@@ -311,8 +311,9 @@ __global__ __launch_bounds__(kBlock) void k_residual_d(Geo g, DeltaBufs<T> D, Co
 // A_z + S_{z-1} + S_{z+1}: 9 LDS reads per component and step, four of them the voxel's corners.
 //
 // Bound by LDS and VALU issue and the latency of a step about equally: at 256^3 the incremental pass
-// moves 1.38 GB in 445 us, 3.1 TB/s (527 us with every node forming its 24 corner forces from
-// stresses passed through LDS, two barriers per step); at 128^3 60 us (89), at 64^3 26 us (36).
+// moves 1.36 GB after a plain iteration and 1.62 GB after an accelerating one, in 427 us on average,
+// 3.5 TB/s (about 520 us with every node forming its 24 corner forces from stresses passed through
+// LDS, two barriers per step); with the launches around it at 128^3 60 us (89), at 64^3 26 us (36).
 // Registers set the blocks per CU: held to four, the incremental pass spills 6 of them and takes
 // 70 us at 128^3; at three nothing spills, which the passes with T stresses are held to as well
 // (those with contact or singular modes would spill).
