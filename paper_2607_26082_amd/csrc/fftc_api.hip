@@ -159,11 +159,11 @@ struct RelaxedCapture {
 };
 
 HostSlot* take_slot() {
-  const RelaxedCapture relaxed;
   std::lock_guard<std::mutex> lk(g_slot_mu);
   for (SlotSlab& b : g_slabs) {
     if (b.used == ~0ull) continue;
     if (!b.base) {
+      const RelaxedCapture relaxed;
       void* p = nullptr;
       if (hipHostMalloc(&p, 64 * kSlotBytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
         (void)hipGetLastError();
@@ -180,13 +180,13 @@ HostSlot* take_slot() {
 
 void give_slot(HostSlot* s) {
   if (!s) return;
-  const RelaxedCapture relaxed;
   std::lock_guard<std::mutex> lk(g_slot_mu);
   for (SlotSlab& b : g_slabs) {
     const ptrdiff_t d = b.base ? (char*)s - b.base : -1;
     if (d < 0 || d >= (ptrdiff_t)(64 * kSlotBytes)) continue;
     b.used &= ~(1ull << (d / (ptrdiff_t)kSlotBytes));
     if (!b.used && &b != g_slabs) {
+      const RelaxedCapture relaxed;
       (void)hipHostFree(b.base);
       b.base = nullptr;
     }
