@@ -289,21 +289,27 @@ struct Layout {
 // square of the length, has met the FFT's: at lengths of the factors 2, 3 and 5 (x passes of
 // 250x64x64 139 against 120 us, the z pass of 128x128x250 403 against 330; x lines of large planes stay:
 // 250x216x216 0.91 of the FFT's time), and at every length below 2048 lines, too few to hide the products'
-// latency (x passes of 252x32x32 1.3).  Other lengths have radices 7, 11 or 13 in the FFT (252x64x64 138
+// latency (x passes of 252x32x32 1.3; not where the plane route below needs them: an iteration of
+// 200x22x26 84 us with both, 89 with neither).  Other lengths have radices 7, 11 or 13 in the FFT (252x64x64 138
 // against 154, 128x128x234 358 against 447); y lines stay (64x250x64 0.83), and FP32 (0.4 to 1.1).
 // Of the compile-time lengths 16, 32 and 48 on grids of at most 160,000 nodes, where
 // the passes are bound by their chain of barriers, in FP32 (at 64^3 167 against 162) and on
 // periodic axes (a y pass at 48^3 periodic 8.4 against 9.2 us in FP64; longer periodic lines the
 // other way: 64^3 12 against 10, 256x256x16 57 against 25, in FP32 57 against 17).
-bool dense_axis(const fftc_problem* h, int J) {
+bool dense_length(const fftc_problem* h, int J) {
   if (h->N[J] > 256) return false;
-  if (h->precision == FFTC_FP64 && J != 1 && h->n[J] >= 190) {
+  return !dtt_compiled(h->n[J]) ||
+         (h->n[J] <= 48 && h->Nn <= 160000 && (h->precision == FFTC_FP32 || h->periodic[J]));
+}
+bool plane_route(const fftc_problem* h);
+bool dense_axis(const fftc_problem* h, int J) {
+  if (!dense_length(h, J)) return false;
+  if (h->precision == FFTC_FP64 && J != 1 && h->n[J] >= 190 && !(J == 0 && plane_route(h))) {
     const long long lines = h->Nn / h->N[J];
     const bool small_radices = h->n[J] % 7 && h->n[J] % 11 && h->n[J] % 13;
     if (lines < 2048 || (small_radices && (J == 2 || lines < 32768))) return false;
   }
-  return !dtt_compiled(h->n[J]) ||
-         (h->n[J] <= 48 && h->Nn <= 160000 && (h->precision == FFTC_FP32 || h->periodic[J]));
+  return true;
 }
 
 // Whether the passes between the x passes run as one launch, a block per (y, z) plane (k_plane), in place of
@@ -313,10 +319,10 @@ bool dense_axis(const fftc_problem* h, int J) {
 // In FP64 only where the products were taken before or are as exact: on the compile-time lengths
 // 32 and 48 the FFT's error on smooth fields is half that of a product (1e-16 against 2e-16).
 bool plane_route(const fftc_problem* h) {
-  if (h->ref_kind == FFTC_REF_ISO || !(dense_axis(h, 0) || dtt_compiled(h->n[0]))) return false;
+  if (h->ref_kind == FFTC_REF_ISO || !(dense_length(h, 0) || dtt_compiled(h->n[0]))) return false;
   if (h->precision == FFTC_FP64)
     for (int J = 1; J < 3; ++J)
-      if (!dense_axis(h, J) && h->n[J] != 16) return false;
+      if (!dense_length(h, J) && h->n[J] != 16) return false;
   const int Ny = h->N[1], Nz = h->N[2];
   const long long ty = (Ny + 15) / 16, tz = (Nz + 15) / 16;
   const long long steps = 2 * ty * tz * ((Ny + 3) / 4 + (Nz + 3) / 4);   // matrix instructions of a plane
